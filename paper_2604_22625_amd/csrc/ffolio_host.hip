@@ -298,6 +298,10 @@ hipError_t fill(void* p, size_t bytes, uint32_t value, hipStream_t hs) {
   return hipGetLastError();
 }
 
+// Copies of the exchange slot for a team of the row-register kernel (fewer, larger
+// workgroups): the same trade, one copy per about 16 workgroups.
+int reg_xgroups(int nwg) { return nwg <= 20 ? 1 : nwg <= 40 ? 2 : nwg <= 80 ? 4 : ffo::XG_MAX; }
+
 // Finite-value check of an optional caller array (warm-start data); sets `bit` in flag.
 __global__ void k_check_finite(const double* x, int64_t cnt, int bit, int* flag) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -403,7 +407,15 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
     }
     if (!placed) return fail(FFO_EINVAL, "problem too large for the per-workgroup working set (reduce m + k or T)");
   }
-  // ---- workspace layout ----
+  // Single-period FP64 solves keep the rows in registers where they fit (up to 160 rows and
+  // one workgroup per compute unit); the options that choose the exchange, the grid or the
+  // per-check output of the general kernel, and impact exponents without a closed prox, stay
+  // with that kernel.  Per iteration there and here: n = 77, 11 rows 15 and 2.8 us; n = 500,
+  // 30 rows 12.9 and 4.3; n = 3000, 22 rows 13.8 and 6.0; n = 5000, 140 rows 14.7 and 6.9.
+  ffo::RegPlan rp{};
+  const bool reg = T == 0 && c.prec == ffo::PREC_FP64 && !opt.deterministic && opt.workgroups == 0 && c.spec &&
+                   opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::reg_plan(n, nr, cus, &rp);
+  // ---- workspace layout (one for both kernels) ----
   const size_t Pn = (size_t)P * n, Tpn = (size_t)Tp * n;
   size_t off = 0;
   auto carve = [&](size_t cnt, size_t elt) { const size_t o = off; off = align_up(off + cnt * elt); return o; };
@@ -426,7 +438,7 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   size_t hoff = 0;
   auto hcarve = [&](size_t bytes) { const size_t o = hoff; hoff = align_up(hoff + bytes); return o; };
   const size_t hOm_o = hcarve(kk * 8), hC_o = hcarve(kk * 8), hW_o = hcarve(2 * kk * 8);
-  const size_t hI_o = hcarve(ffo::INFO_LEN * 8), hF_o = hcarve(8);
+  const size_t hI_o = hcarve(ffo::INFO_LEN * 8), hF_o = hcarve(8), hR_o = hcarve(3 * 256);
   const size_t host_bytes = hoff;
 
   char* B = nullptr;
@@ -500,8 +512,25 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   HIPCHK(fill(B + obar, 8 * ffo::BAR_WORDS, 0u, hs));
   HIPCHK(fill(B + oinfo, ffo::INFO_LEN * 8, 0u, hs));
   HIPCHK(fill(B + ostat, 4, 0xffffffffu, hs));
+  if (reg) {
+    // the kernel reads its records from the (otherwise unused) state arrays
+    static_assert(sizeof(p) <= 256 && sizeof(sv) <= 256 && sizeof(c) <= 256, "one record per state array");
+    c.nwg = nwg = rp.nwg;
+    c.nw = nw = (int)((n + nwg - 1) / nwg);
+    c.xgroups = reg_xgroups(nwg);
+    c.vmax = ffo::reg_vmax(rp.ra);
+    char* hR = H + hR_o;
+    std::memcpy(hR, &p, sizeof(p));
+    std::memcpy(hR + 256, &sv, sizeof(sv));
+    std::memcpy(hR + 512, &c, sizeof(c));
+    HIPCHK(hipMemcpyAsync(B + ost[0], hR, 256, hipMemcpyHostToDevice, hs));
+    HIPCHK(hipMemcpyAsync(B + ost[1], hR + 256, 256, hipMemcpyHostToDevice, hs));
+    HIPCHK(hipMemcpyAsync(B + ost[2], hR + 512, 256, hipMemcpyHostToDevice, hs));
+  }
   if (ev) HIPCHK(hipEventRecord(ev[1], hs));
-  if (int e = ffo::launch_solve(p, sv, c, stream, lds))
+  if (int e = reg ? ffo::launch_reg(rp, (const ffo::DevProblem*)(B + ost[0]), (const ffo::DevState*)(B + ost[1]),
+                                    (const ffo::DevControl*)(B + ost[2]), stream)
+                  : ffo::launch_solve(p, sv, c, stream, lds))
     return fail(FFO_EDEVICE, std::string("cooperative launch of the solve kernel failed: ") +
                                  hipGetErrorString((hipError_t)e));
   if (ev) HIPCHK(hipEventRecord(ev[2], hs));

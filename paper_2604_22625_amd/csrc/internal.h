@@ -139,6 +139,17 @@ int launch_solve_batch(const DevProblem* dp, const DevState* ds, const DevContro
 int solve_batch_occupancy(int kl, int sl, int prec, size_t lds_bytes);
 int solve_vmax(const DevProblem& p);
 
+// Single-period FP64 solve with the constraint rows in registers (reg_kernel.hip): rows in
+// ra groups of 16, 32 ca assets per workgroup, nwg workgroups.  reg_plan returns false where
+// the rows or the assets do not fit (more than 160 rows, or more workgroups than cus).
+struct RegPlan {
+  int ra, ca, nwg;
+};
+bool reg_plan(int64_t n, int nr, int cus, RegPlan* out);
+int reg_vmax(int ra);   // doubles of one copy of the exchange slot
+// One cooperative launch of plan.nwg workgroups; the records are device arrays of one.
+int launch_reg(const RegPlan& plan, const DevProblem* dp, const DevState* ds, const DevControl* dc, void* stream);
+
 // Setup kernels (setup_kernels.hip).
 // Batched form: shared rows K diag(dc) of the n_max-asset universe (unscaled by rows),
 // per-instance row scales drs [B][nr] over each prefix of nb[b] columns (nb on the

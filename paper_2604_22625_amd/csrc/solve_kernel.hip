@@ -39,6 +39,7 @@
 #include <type_traits>
 #include "internal.h"
 #include "cost_math.h"
+#include "wave_ops.h"
 
 namespace ffo {
 namespace {
@@ -55,67 +56,12 @@ constexpr int STW = 2 + 3 * NC;  // published statistics per period
 constexpr int RED_OUT = TB, RED_MAX = TB + 64, RED_LEN = TB + 64 + 16;
 static_assert(TB == 256 || TB == 512, "workgroup size");
 
-__device__ __forceinline__ double ldd(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void std_(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void addd(double* p, double v) {
-  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double sgn(double x) { return (double)((x > 0.0) - (x < 0.0)); }
-
-// Cross-lane moves of a double through DPP (two 32-bit halves; every source lane valid
-// for the controls used here: quad_perm and the row mirrors).
-template <int CTRL>
-__device__ __forceinline__ double dpp(double x) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-constexpr int DPP_SWAP1 = 0xB1;        // quad_perm [1,0,3,2]
-constexpr int DPP_SWAP2 = 0x4E;        // quad_perm [2,3,0,1]
-constexpr int DPP_HALF_MIRROR = 0x141; // lane i <- 7 - i within each 8-lane half-row
-constexpr int DPP_MIRROR = 0x140;      // lane i <- 15 - i within each 16-lane row
-
-// Sums over aligned groups of 4, 8 and 16 lanes; every lane of the group gets the sum.
-__device__ __forceinline__ double sum4(double x) { x += dpp<DPP_SWAP1>(x); return x + dpp<DPP_SWAP2>(x); }
-__device__ __forceinline__ double sum8(double x) { x = sum4(x); return x + dpp<DPP_HALF_MIRROR>(x); }
-__device__ __forceinline__ double sum16(double x) { x = sum8(x); return x + dpp<DPP_MIRROR>(x); }
-__device__ __forceinline__ double max8(double x) {
-  x = fmax(x, dpp<DPP_SWAP1>(x));
-  x = fmax(x, dpp<DPP_SWAP2>(x));
-  return fmax(x, dpp<DPP_HALF_MIRROR>(x));
-}
-__device__ __forceinline__ double max16(double x) { x = max8(x); return fmax(x, dpp<DPP_MIRROR>(x)); }
 template <int L>
 __device__ __forceinline__ double sum_lanes(double x) {
   static_assert(L == 8 || L == 16, "lane group");
   if constexpr (L == 8) return sum8(x);
   else return sum16(x);
 }
-__device__ __forceinline__ double lane_of(double x, int l) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, l);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-// Wave-wide sum / max (fixed order), uniform across the wave.
-__device__ __forceinline__ double wave_sum(double x) {
-  x = sum16(x);
-  return (lane_of(x, 15) + lane_of(x, 31)) + (lane_of(x, 47) + lane_of(x, 63));
-}
-__device__ __forceinline__ double wave_max(double x) {
-  x = max16(x);
-  return fmax(fmax(lane_of(x, 15), lane_of(x, 31)), fmax(lane_of(x, 47), lane_of(x, 63)));
-}
-
-// LDS-qualified element types: indexing through these compiles to ds_read/ds_write
-// instead of generic (flat) memory instructions.
-typedef __attribute__((address_space(3))) double ldbl;
-typedef __attribute__((address_space(3))) int lint;
 // Device-memory pointers in the global address space: their loads count only against
 // vmcnt (generic FLAT loads also count against lgkmcnt, so every LDS wait would drain them).
 template <class T>
@@ -778,13 +724,6 @@ __device__ __forceinline__ double trade_of(const SV& v, const A& x, int t, int l
 // ---------------------------------------------------------------------------------
 // S_t(mu) = sum_i max(|b_ti| - mu, 0) / a_ti with signed b in bb and 1/a in aa.
 
-// Bracket candidates for period t: cen + f_q * hw, f = (-64, -16, -4, -1, 1, 4, 16, 64),
-// clamped at 0.  The central pair (q = 3, 4) is the predicted bracket [lo, hi].
-__device__ __forceinline__ double cand(double cen, double hw, int q) {
-  const double f = (q < 4 ? -1.0 : 1.0) * (double)(1 << (2 * (q < 4 ? 3 - q : q - 4)));
-  return fmax(cen + f * hw, 0.0);
-}
-
 // Statistics of S_t at the bracket candidates for every period t, published at
 // off0 + STW*t: [S(0), max |b|, (S(c_q), A0(c_q), cnt(c_q)) for q < NC] with
 // A0(c) = sum_{|b| > c} 1/a and cnt(c) = #{|b| > c}.  absb/inva: LDS [P][nw] with |b|
@@ -1191,14 +1130,6 @@ __device__ double solve_from_list(const ldbl* buf, int n, double lo, double hi, 
     mu = fmin(fmax(mu, vk), nxt);
   }
   return mu;
-}
-
-// Relative half-width policy after a decision r (see bracket_decide): kept on a hit,
-// shrunk when breakpoints fell inside the central pair, grown when the root was outside.
-__device__ __forceinline__ double adapt_width(int r, double w) {
-  if (r == 1 || r == 2) return w;
-  if (r == 0) return fmax(w * 0.7, 1e-13);
-  return fmin(w * 1.6, 0.25);   // r = 3, 4: the root fell outside the central pair
 }
 
 // Next prediction: centre at the trend mu + (mu - mu_prev), half-width w * mu.
