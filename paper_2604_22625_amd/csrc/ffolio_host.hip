@@ -1069,6 +1069,65 @@ ffo_status launch_teams(const TeamPlan& tp, int W, const std::vector<int>& ckl, 
   return FFO_OK;
 }
 
+// The teams of many single-period FP64 instances on the row-register kernel: one plan (rows
+// and assets per lane) for all, each instance's workgroups, and the ticket order (decreasing
+// size, so that the longest solves start first).
+struct RegTeams {
+  ffo::RegPlan plan{};
+  std::vector<int> g;        // workgroups per instance
+  std::vector<int> inst, rank;
+  int grid = 0;
+};
+
+bool plan_reg_teams(int64_t B, const int64_t* n_b, int nr, int64_t T, int prec, double d, const ffo_options& opt,
+                    int cus, RegTeams* out) {
+  if (T != 0 || prec != ffo::PREC_FP64 || opt.speculative == 0 || opt.verbose >= 2 || !(d == 1.5 || d == 2.0)) return false;
+  int64_t n_max = 0;
+  for (int64_t b = 0; b < B; ++b) n_max = std::max(n_max, n_b[b]);
+  RegTeams& t = *out;
+  if (!ffo::reg_plan(n_max, nr, cus, &t.plan)) return false;
+  const int64_t per = 32 * t.plan.ca;
+  std::vector<int64_t> order(B);
+  int64_t total = 0;
+  t.g.resize(B);
+  for (int64_t b = 0; b < B; ++b) {
+    order[b] = b;
+    t.g[b] = (int)((n_b[b] + per - 1) / per);
+    total += t.g[b];
+  }
+  if (total > (1 << 30)) return false;
+  std::stable_sort(order.begin(), order.end(), [&](int64_t a, int64_t b) { return n_b[a] > n_b[b]; });
+  t.inst.reserve(total);
+  t.rank.reserve(total);
+  for (int64_t b : order)
+    for (int w = 0; w < t.g[b]; ++w) { t.inst.push_back((int)b); t.rank.push_back(w); }
+  t.grid = (int)std::min<int64_t>(total, cus);
+  return true;
+}
+
+// The tables to the device and the one launch (the staging lives until the call's last wait).
+ffo_status launch_reg_teams(const RegTeams& t, const char* dP, const char* dS, const char* dCt, char* dinst, char* drank,
+                            char* dnext, char* hinst, char* hrank, void* stream) {
+  hipStream_t hs = (hipStream_t)stream;
+  const size_t bytes = t.inst.size() * 4;
+  std::memcpy(hinst, t.inst.data(), bytes);
+  std::memcpy(hrank, t.rank.data(), bytes);
+  HIPCHK(hipMemcpyAsync(dinst, hinst, bytes, hipMemcpyHostToDevice, hs));
+  HIPCHK(hipMemcpyAsync(drank, hrank, bytes, hipMemcpyHostToDevice, hs));
+  if (int e = ffo::launch_reg_queue(t.plan, (const ffo::DevProblem*)dP, (const ffo::DevState*)dS,
+                                    (const ffo::DevControl*)dCt, (const int*)dinst, (const int*)drank,
+                                    (int)t.inst.size(), (int*)dnext, t.grid, stream))
+    return fail(FFO_EDEVICE, std::string("cooperative launch of the batched solve kernel failed: ") +
+                                 hipGetErrorString((hipError_t)e));
+  return FFO_OK;
+}
+
+// Doubles of instance b's exchange buffer and barrier words on that kernel.
+size_t reg_xbuf_doubles(const RegTeams& t, int64_t b) { return (size_t)3 * reg_xgroups(t.g[b]) * ffo::reg_vmax(t.plan.ra); }
+// (each barrier on cache lines of its own: ten teams' counters on one line took 10.1 us per
+// iteration at n = 5000, 7.4 apart)
+size_t reg_bar_words(const RegTeams& t, int64_t b) { return reg_xgroups(t.g[b]) > 1 ? ffo::BAR_WORDS : ffo::XGSTRIDE; }
+
 // Statuses and infos of every instance after the team launches; returns the most severe
 // status (FFO_EDEVICE > FFO_NUMERIC > FFO_INFEASIBLE > FFO_TIMEOUT > FFO_NOT_CONVERGED).
 // verbose: the slowest instance's phase times on stderr (verbose >= 2: every instance's).
@@ -1514,7 +1573,9 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const int W = occ * cus;
   // instances in decreasing size, cut into launches whose minimal teams fit the resident grid
   const TeamPlan tp = plan_teams(B, n_b, W, NW_MAX, NW_MIN);
-  const std::vector<int>& g = tp.g;
+  RegTeams rt;
+  const bool reg = plan_reg_teams(B, n_b, nr, 0, prec, d, opt, cus, &rt);
+  const std::vector<int>& g = reg ? rt.g : tp.g;
   const auto& chunks = tp.chunks;
 
   // ---- workspace layout ----
@@ -1530,10 +1591,16 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t odrs = carve((size_t)B * std::max(nr, 1), 8), oca = carve(N, 8), ocb = carve(N, 8);
   size_t ost[9];
   for (auto& o : ost) o = carve(N, 8);
-  const size_t oxb = carve((size_t)B * 3 * c0.vmax, 8), obar = carve(B, 8);
+  std::vector<size_t> xoff(B + 1, 0), boff(B + 1, 0);   // exchange buffer and barrier of each instance
+  for (int64_t b = 0; b < B; ++b) {
+    xoff[b + 1] = xoff[b] + (reg ? reg_xbuf_doubles(rt, b) : (size_t)3 * c0.vmax);
+    boff[b + 1] = boff[b] + (reg ? reg_bar_words(rt, b) : 1);
+  }
+  const size_t oxb = carve(xoff[B], 8), obar = carve(boff[B], 8);
   const size_t oinfo = carve((size_t)B * ffo::INFO_LEN, 8), ostat = carve(B, 4), oflag = carve(1, 4);
   const size_t oP = carve(B, sizeof(ffo::DevProblem)), oS = carve(B, sizeof(ffo::DevState));
-  const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(W, 4), orank = carve(W, 4);
+  const size_t nslot = std::max<size_t>(W, rt.inst.size());
+  const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(nslot, 4), orank = carve(nslot, 4), onext = carve(1, 4);
   const size_t total = off;
   size_t hoff = 0;
   auto hcarve = [&](size_t bytes) { const size_t o = hoff; hoff = align_up(hoff + bytes); return o; };
@@ -1541,7 +1608,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t hflag_o = hcarve(4), hinfo_o = hcarve((size_t)B * ffo::INFO_LEN * 8), hstat_o = hcarve((size_t)B * 4);
   const size_t hP_o = hcarve((size_t)B * sizeof(ffo::DevProblem)), hS_o = hcarve((size_t)B * sizeof(ffo::DevState));
   const size_t hCt_o = hcarve((size_t)B * sizeof(ffo::DevControl)), hnb_o = hcarve((size_t)B * 8);
-  const size_t hteam_o = hcarve((size_t)W * 4 * chunks.size()), hrank_o = hcarve((size_t)W * 4 * chunks.size());
+  const size_t hteam_o = hcarve(nslot * 4 * chunks.size()), hrank_o = hcarve(nslot * 4 * chunks.size());
   const size_t host_bytes = hoff;
 
   Workspace* ws = nullptr;
@@ -1586,8 +1653,9 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     return fail(FFO_EDEVICE, "setup kernel launch failed");
   HIPCHK(hipMemsetAsync(Bd + obF, 0, (size_t)std::max<int64_t>(k, 1) * 8, hs));
   HIPCHK(hipMemsetAsync(Bd + ocr, 0, 8, hs));
-  HIPCHK(hipMemsetAsync(Bd + oxb, 0, (size_t)B * 3 * c0.vmax * 8, hs));
-  HIPCHK(hipMemsetAsync(Bd + obar, 0, (size_t)B * 8, hs));
+  HIPCHK(hipMemsetAsync(Bd + oxb, 0, xoff[B] * 8, hs));
+  HIPCHK(hipMemsetAsync(Bd + obar, 0, boff[B] * 8, hs));
+  HIPCHK(hipMemsetAsync(Bd + onext, 0, 4, hs));
   HIPCHK(hipMemsetAsync(Bd + oinfo, 0, (size_t)B * ffo::INFO_LEN * 8, hs));
   HIPCHK(hipMemsetAsync(Bd + ostat, 0xff, (size_t)B * 4, hs));
 
@@ -1609,7 +1677,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     sv.xs = D(ost[0]) + o; sv.x0s = D(ost[1]) + o; sv.Txs = D(ost[2]) + o;
     sv.bb = D(ost[3]) + o; sv.aa = D(ost[4]) + o; sv.vpow = D(ost[5]) + o;
     sv.ysC = D(ost[6]) + o; sv.ys0C = D(ost[7]) + o; sv.TysC = D(ost[8]) + o;
-    sv.xbuf = D(oxb) + (size_t)b * 3 * c0.vmax; sv.bar = (unsigned long long*)(Bd + obar) + b;
+    sv.xbuf = D(oxb) + xoff[b]; sv.bar = (unsigned long long*)(Bd + obar) + boff[b];
     sv.info = D(oinfo) + (size_t)b * ffo::INFO_LEN; sv.status = (int32_t*)(Bd + ostat) + b;
     sv.w_out = w_out + o; sv.y_out = nullptr;
     hS[b] = sv;
@@ -1617,19 +1685,22 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     c.nwg = g[b];
     c.nw = (int)((n_b[b] + g[b] - 1) / g[b]);
     c.xmode = g[b] == 1 ? ffo::XM_LOCAL : ffo::XM_ATOMIC;
+    if (reg) { c.xgroups = reg_xgroups(g[b]); c.vmax = ffo::reg_vmax(rt.plan.ra); }
     hCt[b] = c;
   }
   std::vector<int> ckl, csl;
   std::vector<size_t> clds;
-  place_teams(tp, hP, hCt, prec, std::min<size_t>(prop.sharedMemPerBlock, 160 * 1024), cus, ckl, csl, clds);
+  if (!reg) place_teams(tp, hP, hCt, prec, std::min<size_t>(prop.sharedMemPerBlock, 160 * 1024), cus, ckl, csl, clds);
   HIPCHK(hipMemcpyAsync(Bd + oP, hP, (size_t)B * sizeof(ffo::DevProblem), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
   HIPCHK(hipEventRecord(ws->ev[1], hs));
-  if (ffo_status st = launch_teams(tp, W, ckl, csl, clds, prec, (const ffo::DevProblem*)(Bd + oP),
-                                   (const ffo::DevState*)(Bd + oS), (const ffo::DevControl*)(Bd + oCt),
-                                   (int*)(Bd + oteam), (int*)(Bd + orank), (int*)(Hb + hteam_o),
-                                   (int*)(Hb + hrank_o), stream))
+  if (ffo_status st = reg ? launch_reg_teams(rt, Bd + oP, Bd + oS, Bd + oCt, Bd + oteam, Bd + orank, Bd + onext, Hb + hteam_o,
+                                             Hb + hrank_o, stream)
+                          : launch_teams(tp, W, ckl, csl, clds, prec, (const ffo::DevProblem*)(Bd + oP),
+                                         (const ffo::DevState*)(Bd + oS), (const ffo::DevControl*)(Bd + oCt),
+                                         (int*)(Bd + oteam), (int*)(Bd + orank), (int*)(Hb + hteam_o),
+                                         (int*)(Hb + hrank_o), stream))
     return st;
   HIPCHK(hipEventRecord(ws->ev[2], hs));
   double* hinfo = (double*)(Hb + hinfo_o);
@@ -1643,8 +1714,9 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   if (opt.verbose)
     std::fprintf(stderr,
                  "[ffo batch] B %lld launches %zu resident %d (occupancy %d) lds %zu | first launch: slice in LDS %d, "
-                 "state in LDS %d, %zu bytes | setup %.3f ms solve %.3f ms\n",
-                 (long long)B, chunks.size(), W, occ, lds_cap, ckl[0], csl[0], clds[0], ms_setup, ms_iter);
+                 "state in LDS %d (2: registers), %zu bytes | setup %.3f ms solve %.3f ms\n",
+                 (long long)B, reg ? 1 : chunks.size(), reg ? rt.grid : W, occ, lds_cap, reg ? 2 : ckl[0], reg ? 2 : csl[0],
+                 reg ? 0 : clds[0], ms_setup, ms_iter);
   return collect_teams(B, n_b, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
 }
 
@@ -1724,6 +1796,12 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   if (occ < 1) return fail(FFO_EDEVICE, "the batched solve kernel cannot be resident");
   const int W = occ * cus;
   const TeamPlan tp = plan_teams(B, n, W, NW_MAX, NW_MIN);
+  // single-period FP64 markets on the row-register kernel (ten n = 5000 markets, 140 rows:
+  // 271 ms in the general team kernel, whose 25 workgroups per market read their rows from device
+  // memory, 30 ms here)
+  RegTeams rt;
+  const bool reg = plan_reg_teams(B, n, nr, T, prec, d, opt, cus, &rt);
+  const std::vector<int>& g = reg ? rt.g : tp.g;
 
   // ---- workspace: each instance's scaled rows, scales, costs and state, as ffo_solve's ----
   struct Inst {
@@ -1744,10 +1822,16 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
     r.bF = carve(std::max<int64_t>(k, 1), 8); r.cr = carve(1, 8); r.C = carve(std::max<int64_t>(k * k, 1), 8);
     for (int j = 0; j < 9; ++j) r.st[j] = carve((j < 6 ? P : Tp) * nb, 8);   // 6 primal [P][n], 3 trade [T][n]
   }
-  const size_t oxb = carve((size_t)B * 3 * c0.vmax, 8), obar = carve(B, 8);
+  std::vector<size_t> xoff(B + 1, 0), boff(B + 1, 0);   // exchange buffer and barrier of each instance
+  for (int64_t b = 0; b < B; ++b) {
+    xoff[b + 1] = xoff[b] + (reg ? reg_xbuf_doubles(rt, b) : (size_t)3 * c0.vmax);
+    boff[b + 1] = boff[b] + (reg ? reg_bar_words(rt, b) : 1);
+  }
+  const size_t oxb = carve(xoff[B], 8), obar = carve(boff[B], 8);
   const size_t oinfo = carve((size_t)B * ffo::INFO_LEN, 8), ostat = carve(B, 4), oflag = carve(1, 4);
   const size_t oP = carve(B, sizeof(ffo::DevProblem)), oS = carve(B, sizeof(ffo::DevState));
-  const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(W, 4), orank = carve(W, 4);
+  const size_t nslot = std::max<size_t>(W, rt.inst.size());
+  const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(nslot, 4), orank = carve(nslot, 4), onext = carve(1, 4);
   const size_t total = off;
   const size_t kk = (size_t)std::max<int64_t>(k * k, 1);
   size_t hoff = 0;
@@ -1756,7 +1840,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   const size_t hflag_o = hcarve(4), hinfo_o = hcarve((size_t)B * ffo::INFO_LEN * 8), hstat_o = hcarve((size_t)B * 4);
   const size_t hP_o = hcarve((size_t)B * sizeof(ffo::DevProblem)), hS_o = hcarve((size_t)B * sizeof(ffo::DevState));
   const size_t hCt_o = hcarve((size_t)B * sizeof(ffo::DevControl));
-  const size_t hteam_o = hcarve((size_t)W * 4 * tp.chunks.size()), hrank_o = hcarve((size_t)W * 4 * tp.chunks.size());
+  const size_t hteam_o = hcarve(nslot * 4 * tp.chunks.size()), hrank_o = hcarve(nslot * 4 * tp.chunks.size());
   const size_t host_bytes = hoff;
 
   Workspace* ws = nullptr;
@@ -1815,33 +1899,37 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
     sv.xs = D(r.st[0]); sv.x0s = D(r.st[1]); sv.Txs = D(r.st[2]);
     sv.bb = D(r.st[3]); sv.aa = D(r.st[4]); sv.vpow = D(r.st[5]);
     sv.ysC = D(r.st[6]); sv.ys0C = D(r.st[7]); sv.TysC = D(r.st[8]);
-    sv.xbuf = D(oxb) + (size_t)b * 3 * c0.vmax; sv.bar = (unsigned long long*)(Bd + obar) + b;
+    sv.xbuf = D(oxb) + xoff[b]; sv.bar = (unsigned long long*)(Bd + obar) + boff[b];
     sv.info = D(oinfo) + (size_t)b * ffo::INFO_LEN; sv.status = (int32_t*)(Bd + ostat) + b;
     sv.w_out = w_out[b]; sv.y_out = nullptr;
     hS[b] = sv;
     ffo::DevControl c = c0;
-    c.nwg = tp.g[b];
-    c.nw = (int)((n[b] + tp.g[b] - 1) / tp.g[b]);
-    c.xmode = tp.g[b] == 1 ? ffo::XM_LOCAL : ffo::XM_ATOMIC;
+    c.nwg = g[b];
+    c.nw = (int)((n[b] + g[b] - 1) / g[b]);
+    c.xmode = g[b] == 1 ? ffo::XM_LOCAL : ffo::XM_ATOMIC;
+    if (reg) { c.xgroups = reg_xgroups(g[b]); c.vmax = ffo::reg_vmax(rt.plan.ra); }
     hCt[b] = c;
   }
-  HIPCHK(fill(Bd + oxb, (size_t)B * 3 * c0.vmax * 8, 0u, hs));
-  HIPCHK(fill(Bd + obar, (size_t)B * 8, 0u, hs));
+  HIPCHK(fill(Bd + oxb, xoff[B] * 8, 0u, hs));
+  HIPCHK(fill(Bd + obar, boff[B] * 8, 0u, hs));
+  HIPCHK(fill(Bd + onext, 4, 0u, hs));
   HIPCHK(fill(Bd + oinfo, (size_t)B * ffo::INFO_LEN * 8, 0u, hs));
   HIPCHK(fill(Bd + ostat, (size_t)B * 4, 0xffffffffu, hs));
 
   // ---- LDS placement, records to the device, one cooperative launch per chunk ----
   std::vector<int> ckl, csl;
   std::vector<size_t> clds;
-  place_teams(tp, hP, hCt, prec, lds_lim, cus, ckl, csl, clds);
+  if (!reg) place_teams(tp, hP, hCt, prec, lds_lim, cus, ckl, csl, clds);
   HIPCHK(hipMemcpyAsync(Bd + oP, hP, (size_t)B * sizeof(ffo::DevProblem), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
   HIPCHK(hipEventRecord(ws->ev[1], hs));
-  if (ffo_status st = launch_teams(tp, W, ckl, csl, clds, prec, (const ffo::DevProblem*)(Bd + oP),
-                                   (const ffo::DevState*)(Bd + oS), (const ffo::DevControl*)(Bd + oCt),
-                                   (int*)(Bd + oteam), (int*)(Bd + orank), (int*)(Hb + hteam_o),
-                                   (int*)(Hb + hrank_o), stream))
+  if (ffo_status st = reg ? launch_reg_teams(rt, Bd + oP, Bd + oS, Bd + oCt, Bd + oteam, Bd + orank, Bd + onext, Hb + hteam_o,
+                                             Hb + hrank_o, stream)
+                          : launch_teams(tp, W, ckl, csl, clds, prec, (const ffo::DevProblem*)(Bd + oP),
+                                         (const ffo::DevState*)(Bd + oS), (const ffo::DevControl*)(Bd + oCt),
+                                         (int*)(Bd + oteam), (int*)(Bd + orank), (int*)(Hb + hteam_o),
+                                         (int*)(Hb + hrank_o), stream))
     return st;
   HIPCHK(hipEventRecord(ws->ev[2], hs));
   double* hinfo = (double*)(Hb + hinfo_o);
@@ -1855,8 +1943,9 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   if (opt.verbose)
     std::fprintf(stderr,
                  "[ffo many] B %lld launches %zu resident %d (occupancy %d) | first launch: slice in LDS %d, state in "
-                 "LDS %d, %zu bytes | setup %.3f ms solve %.3f ms\n",
-                 (long long)B, tp.chunks.size(), W, occ, ckl[0], csl[0], clds[0], ms_setup, ms_iter);
+                 "LDS %d (2: registers), %zu bytes | setup %.3f ms solve %.3f ms\n",
+                 (long long)B, reg ? 1 : tp.chunks.size(), reg ? rt.grid : W, occ, reg ? 2 : ckl[0], reg ? 2 : csl[0],
+                 reg ? 0 : clds[0], ms_setup, ms_iter);
   return collect_teams(B, n, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
 }
 

@@ -149,6 +149,11 @@ bool reg_plan(int64_t n, int nr, int cus, RegPlan* out);
 int reg_vmax(int ra);   // doubles of one copy of the exchange slot
 // One cooperative launch of plan.nwg workgroups; the records are device arrays of one.
 int launch_reg(const RegPlan& plan, const DevProblem* dp, const DevState* ds, const DevControl* dc, void* stream);
+// Many instances in one cooperative launch of `grid` workgroups (at most one per compute
+// unit), which take tickets: ticket t is workgroup rank[t] of instance inst[t], an instance's
+// tickets one after another.  next: one zeroed int.
+int launch_reg_queue(const RegPlan& plan, const DevProblem* dp, const DevState* ds, const DevControl* dc, const int* inst,
+                     const int* rank, int tickets, int* next, int grid, void* stream);
 
 // Setup kernels (setup_kernels.hip).
 // Batched form: shared rows K diag(dc) of the n_max-asset universe (unscaled by rows),

@@ -105,7 +105,8 @@ __device__ __forceinline__ double wave_parts(const RegLds<RA, CA>& L, int j, boo
 // j = 1); exchange_end then frees the slot.  A single workgroup only synchronises: part
 // holds everything, and must not be written again before the next barrier.
 template <int RA, int CA>
-__device__ __forceinline__ bool exchange_begin(RegX& X, RegLds<RA, CA>& L, int tid, int V, bool mx) {
+__device__ __forceinline__ bool exchange_begin(RegX& X, RegLds<RA, CA>& L, int tid, int V, bool mx,
+                                               uint32_t spin_limit) {
   __syncthreads();   // every wave's partial sums are in part
   if (X.nwg == 1) return true;
   gptr<double> cur = X.xbuf + (size_t)(X.at * X.ng * X.vmax);
@@ -142,7 +143,7 @@ __device__ __forceinline__ bool exchange_begin(RegX& X, RegLds<RA, CA>& L, int t
     int ok = 1;
     while (__hip_atomic_load(poll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
       if (++spins > 64) __builtin_amdgcn_s_sleep(1);
-      if (spins > X.spin_limit) { ok = 0; break; }
+      if (spins >= spin_limit) { ok = 0; break; }
     }
     L.ok = ok;
   }
@@ -179,8 +180,8 @@ __device__ __forceinline__ void exchange_end(RegX& X, int tid) {
 
 // The whole exchange, totals to LDS.
 template <int RA, int CA>
-__device__ __forceinline__ bool exchange(RegX& X, RegLds<RA, CA>& L, int tid, int V, bool mx) {
-  if (!exchange_begin(X, L, tid, V, mx)) return false;
+__device__ __forceinline__ bool exchange(RegX& X, RegLds<RA, CA>& L, int tid, int V, bool mx, uint32_t spin_limit) {
+  if (!exchange_begin(X, L, tid, V, mx, spin_limit)) return false;
   if (tid < V) L.tot[tid] = total(X, L, tid, mx);
   exchange_end(X, tid);
   __syncthreads();
@@ -353,7 +354,7 @@ __device__ __forceinline__ bool multisect(RegX& X, RegLds<RA, CA>& L, double lo,
     }
     S += dpp<DPP_SWAP1>(S); A0 += dpp<DPP_SWAP1>(A0); N += dpp<DPP_SWAP1>(N);
     if (sub == 0) { L.part[wave][3 * q] = S; L.part[wave][3 * q + 1] = A0; L.part[wave][3 * q + 2] = N; }
-    if (!exchange(X, L, tid, 3 * MSC, false)) return false;
+    if (!exchange(X, L, tid, 3 * MSC, false, X.spin_limit)) return false;
     const double* T0 = L.tot;
     const unsigned long long ge = __ballot(lane < MSC && T0[3 * (lane < MSC ? lane : 0)] >= 1.0);
     const int qs = ge ? 63 - __clzll((long long)ge) : 0;
@@ -456,7 +457,7 @@ __device__ __forceinline__ Place place(int tid0, int nwa, int nr) {
 
 template <int RA, int CA>
 __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* sp, const DevControl* cp, int wg,
-                                         RegLds<RA, CA>& L) {
+                                         RegLds<RA, CA>& L, uint32_t first_spins) {
   const DevProblem& p = *pp;
   const DevState& s = *sp;
   const DevControl& ctl = *cp;
@@ -519,7 +520,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
     __syncthreads();
   }
 
-  const long long t_start = wall_clock64();
+  long long t_start = wall_clock64();
   long long t_check = 0;
   double omega = ctl.omega0 > 0.0 ? ctl.omega0 : 1.0, r0 = -1.0, rprev = INFINITY;
   long long it = 0;
@@ -539,7 +540,8 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
       const double a = wave_sum(mine ? v * v : 0.0), b = wave_sum(mine ? dc * v * dc * v : 0.0);
       if (lane == 0) { L.part[wave][0] = a; L.part[wave][1] = b; }
       rows1(K, v, L.part[wave] + OR, tid);
-      if (!exchange(X, L, tid, OS, false)) goto fail;
+      if (!exchange(X, L, tid, OS, false, pw == 0 ? first_spins : X.spin_limit)) goto fail;
+      if (pw == 0) t_start = wall_clock64();   // the team is complete
       double kv = 0.0;
       for (int r = lane; r < NRP; r += 64) kv = fma(L.tot[OR + r], L.tot[OR + r], kv);
       kv = wave_sum(kv) + L.tot[1];
@@ -586,7 +588,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
           const double x1 = 2.0 * (ab > c4 ? g * (ab - c4) : 0.0) - x, x2 = ab > c4 ? -g : 0.0;
           rows2(K, val ? x1 : 0.0, val ? x2 : 0.0, L.part[wave] + OR, tid);
         }
-        if (!exchange_begin(X, L, tid, OR + 2 * NRP, true)) goto fail;
+        if (!exchange_begin(X, L, tid, OR + 2 * NRP, true, X.spin_limit)) goto fail;
         const double st = total(X, L, lane < NST ? lane : 0, true);
         double kx = 0.0, p2 = 0.0;
         if (rown) {
@@ -608,7 +610,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
           else if (!multisect(X, L, lo, hi, mu, tid)) goto fail;
           const double xh = ab > mu ? copysign(gia, b) * (ab - mu) : 0.0;
           rows1(K, val ? 2.0 * xh - x : 0.0, L.part[wave] + OR, tid);
-          if (!exchange_begin(X, L, tid, OS, false)) goto fail;
+          if (!exchange_begin(X, L, tid, OS, false, X.spin_limit)) goto fail;
           if (rown) kx = total(X, L, OR + tid, false);
           exchange_end(X, tid);
         }
@@ -688,7 +690,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
           if (rg < CA) { L.ab[wave][slot] = val ? abd : 0.0; L.ia[wave][slot] = val ? iad : 0.0; }
           __builtin_amdgcn_wave_barrier();
           stats<WA>(L.ab[wave], L.ia[wave], dcen, dhw, L.part[wave], tid);
-          if (!exchange(X, L, tid, OS + NSC, true)) goto fail;
+          if (!exchange(X, L, tid, OS + NSC, true, X.spin_limit)) goto fail;
           if (tid < NSC) L.c1[tid] = L.tot[OS + tid];   // (read after the barriers of wg_total)
           double dlo = 0.0, dhi = 0.0, dm = 0.0;
           const int rd = decide(L.tot[lane < NST ? lane : 0], dcen, dhw, dlo, dhi, dm, tid);
@@ -731,7 +733,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
             }
             if (lane == 0) { L.part[wave][0] = iv; L.part[wave][1] = am; }
           }
-          if (!exchange(X, L, tid, 2, true)) goto fail;
+          if (!exchange(X, L, tid, 2, true, X.spin_limit)) goto fail;
           bool infeasible = false;
           if (inf_test) {   // a Farkas certificate for the feasible set (see solve_kernel.hip)
             double sup = 0.0, mag = 0.0;
@@ -845,15 +847,37 @@ template <int RA, int CA>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_reg(
     const DevProblem* __restrict__ dp, const DevState* __restrict__ ds, const DevControl* __restrict__ dc) {
   __shared__ RegLds<RA, CA> L;
-  reg_body<RA, CA>(dp, ds, dc, blockIdx.x, L);
+  reg_body<RA, CA>(dp, ds, dc, blockIdx.x, L, dc->spin_limit);
+}
+
+// Many instances: resident workgroups take (instance, rank) tickets in order, an instance's
+// ranks one after another, so at any time the unfinished instance with the first tickets
+// has all its workgroups running or about to be taken up by those that finish earlier
+// ones: every team completes, whatever the sizes.  A team's first wait is for that.
+template <int RA, int CA>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_reg_queue(
+    const DevProblem* __restrict__ dp, const DevState* __restrict__ ds, const DevControl* __restrict__ dc,
+    const int* __restrict__ inst, const int* __restrict__ rank, int tickets, int* next) {
+  __shared__ RegLds<RA, CA> L;
+  __shared__ int s_t;
+  while (true) {
+    __syncthreads();
+    if (threadIdx.x == 0) s_t = __hip_atomic_fetch_add(next, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane(s_t);
+    if (t >= tickets) return;
+    const int b = inst[t];
+    reg_body<RA, CA>(dp + b, ds + b, dc + b, rank[t], L, 0xffffffffu);
+  }
 }
 
 }  // namespace
 
 // Row groups of 16 and assets per lane group instantiated: RA x CA doubles of rows per
 // lane, at most 80 (160 of the 256 registers).
-static const void* reg_fn(int ra, int ca) {
-#define FFO_REG(R, C) if (ra == R && ca == C) return (const void*)k_reg<R, C>;
+static const void* reg_fn(int ra, int ca, bool queue) {
+#define FFO_REG(R, C) \
+  if (ra == R && ca == C) return queue ? (const void*)k_reg_queue<R, C> : (const void*)k_reg<R, C>;
   FFO_REG(1, 4) FFO_REG(1, 8) FFO_REG(1, 16)
   FFO_REG(2, 4) FFO_REG(2, 8) FFO_REG(2, 16)
   FFO_REG(3, 8) FFO_REG(3, 16)
@@ -874,9 +898,9 @@ bool reg_plan(int64_t n, int nr, int cus, RegPlan* out) {
     if (16 * r >= nr) { ra = r; break; }
   if (!ra) return false;
   for (int ca : {4, 8, 16}) {
-    if (!reg_fn(ra, ca)) continue;
+    if (!reg_fn(ra, ca, false)) continue;
     const int64_t g = (n + 32 * ca - 1) / (32 * ca);
-    const bool last = !reg_fn(ra, 2 * ca);
+    const bool last = !reg_fn(ra, 2 * ca, false);
     if (g > (last ? cus : 1)) continue;
     out->ra = ra;
     out->ca = ca;
@@ -888,7 +912,14 @@ bool reg_plan(int64_t n, int nr, int cus, RegPlan* out) {
 
 int launch_reg(const RegPlan& pl, const DevProblem* dp, const DevState* ds, const DevControl* dc, void* stream) {
   void* args[] = {(void*)&dp, (void*)&ds, (void*)&dc};
-  const hipError_t e = hipLaunchCooperativeKernel(reg_fn(pl.ra, pl.ca), dim3(pl.nwg), dim3(NT), args, 0, (hipStream_t)stream);
+  const hipError_t e = hipLaunchCooperativeKernel(reg_fn(pl.ra, pl.ca, false), dim3(pl.nwg), dim3(NT), args, 0, (hipStream_t)stream);
+  return e == hipSuccess ? 0 : (int)e;
+}
+
+int launch_reg_queue(const RegPlan& pl, const DevProblem* dp, const DevState* ds, const DevControl* dc, const int* inst,
+                     const int* rank, int tickets, int* next, int grid, void* stream) {
+  void* args[] = {(void*)&dp, (void*)&ds, (void*)&dc, (void*)&inst, (void*)&rank, (void*)&tickets, (void*)&next};
+  const hipError_t e = hipLaunchCooperativeKernel(reg_fn(pl.ra, pl.ca, true), dim3(grid), dim3(NT), args, 0, (hipStream_t)stream);
   return e == hipSuccess ? 0 : (int)e;
 }
 

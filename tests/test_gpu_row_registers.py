@@ -82,3 +82,17 @@ def test_warm_start_one_sided_bounds_and_cut_off(n):
     for y, yg in zip(Y, Yg):
         assert float((y - yg).abs().max()) <= 1e-10 * max(1e-3, float(yg.abs().max()))
     _agree(inst, *_both(inst, w_init=W, y_init=Y, omega_init=i.omega))
+
+
+def test_many_markets_share_the_queue():
+    """More workgroups than compute units, sizes from one asset to several workgroups: the
+    tickets run in several waves and every market gets its own solve's result."""
+    ff = _gpu()
+    insts = [make_single(n, 6, 11, seed=100 + j) for j, n in enumerate([1, 5, 4000, 700, 513, 512, 129] * 20)]
+    print(f"[case] many {len(insts)}", flush=True)
+    Ws, infos = ff.solve_many(insts, tol=TOL, time_limit_s=20.0, max_iter=100_000)
+    torch.cuda.synchronize()
+    for j in (0, 1, 2, 3, 4, 5, 6, 72, len(insts) - 1):
+        W, i = ff.solve_instance(insts[j], tol=TOL, time_limit_s=20.0, max_iter=100_000)
+        assert infos[j].status == 0 and infos[j].iters == i.iters
+        assert float((W - Ws[j]).abs().max()) <= 1e-10 * float(W.abs().max())
