@@ -100,10 +100,10 @@ typedef struct {
                               the solve kernel's loop on its own team of workgroups);
                               2: the lockstep form (every unconverged instance advances one
                               iteration per step, the products over the shared rows run as
-                              float64 matrix-core GEMMs; FFO_FP64 only); 0 (default): the
-                              lockstep form when it applies (FFO_FP64, m + k <= 160),
-                              else the team form                                      */
-  int32_t autotune;        /* lockstep form only.  1 (default): on the first solve of a shape
+                              float64 matrix-core GEMMs; FFO_FP64 only); 0 (default): where
+                              the lockstep form applies (FFO_FP64, m + k <= 160) its results,
+                              from whichever form computes them faster, else the team form */
+  int32_t autotune;        /* lockstep form's kernels only.  1 (default): on the first solve of a shape
                               the library times a few tile sizes and kernel arrangements and
                               keeps the fastest for later solves of that shape; -1: fixed
                               defaults (the element passes as kernels of their own); 0:

@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <string>
@@ -267,6 +268,15 @@ ffo_status status_of(int32_t hstat) {
     case ffo::DS_INFEASIBLE: return FFO_INFEASIBLE;
     default: return FFO_EDEVICE;
   }
+}
+
+// The more severe of two instance statuses.
+ffo_status worse(ffo_status a, ffo_status b) {
+  auto rank = [](ffo_status x) {
+    return x == FFO_EDEVICE ? 5 : x == FFO_NUMERIC ? 4 : x == FFO_INFEASIBLE ? 3 : x == FFO_TIMEOUT ? 2
+           : x == FFO_NOT_CONVERGED ? 1 : 0;
+  };
+  return rank(b) > rank(a) ? b : a;
 }
 
 // Fill `words` 32-bit words with `value` (used instead of hipMemsetAsync so that a caller
@@ -660,6 +670,37 @@ hipError_t ls_start(const ffo::LsShared& S, const LsTune& tu, int gA, int gC, co
   return (hipError_t)r;
 }
 
+// The largest number of instances left at a check that finish on the plain solve, each
+// warm started from its iterate and primal weight there.  In the lockstep form a step with
+// a handful of instances still pays every kernel's launch and latency (about 41 us against
+// ~12 us for an iteration of the plain kernel).
+constexpr int64_t kHandoff = 4;
+
+// Finishes instance b (n_b assets at offset o of the packed vectors) on the plain solve from
+// the iterate (w, y) after `it` iterations; rows: scratch for its m exposure rows.
+ffo_status finish_plain(int64_t b, int64_t nb, int64_t o, int64_t n_max, int64_t k, int64_t m, const double* F,
+                        const double* Omega, const double* delta, const double* A, const double* alpha,
+                        const double* s, const double* q, const double* w0, const double* L, const double* U, double d,
+                        double GMV, double lambda1, double lambda2, double lambda3, const ffo_options& opt,
+                        const double* w, const double* y, double omega, int64_t it, int64_t restarts, double* rows,
+                        hipStream_t st, double* w_out, ffo_info* info) {
+  if (m > 0)
+    HIPCHK(hipMemcpy2DAsync(rows, (size_t)nb * 8, A, (size_t)n_max * 8, (size_t)nb * 8, (size_t)m,
+                            hipMemcpyDeviceToDevice, st));
+  ffo_options o2 = opt;
+  o2.max_iter = std::max<int64_t>(1, opt.max_iter - it);
+  o2.workgroups = 0;
+  o2.verbose = 0;
+  *info = ffo_info{};
+  const ffo_status sb = solve_impl(nb, k, m, 0, alpha + o, F, Omega, delta, s + o, q + o, d, rows,
+                                   m ? L + (size_t)b * m : nullptr, m ? U + (size_t)b * m : nullptr, w0 + o, GMV, lambda1,
+                                   lambda2, lambda3, nullptr, w, y, omega, &o2, st, w_out + o, nullptr, info, nullptr);
+  if (sb == FFO_EINVAL || sb == FFO_ENOMEM || sb == FFO_EDEVICE) return sb;
+  info->iters += it;
+  info->restarts += restarts;
+  return FFO_OK;
+}
+
 ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_t k, int64_t m, const double* F,
                             const double* Omega, const double* delta, const double* A, const int64_t* offs,
                             const double* alpha, const double* s, const double* q, const double* w0,
@@ -857,11 +898,6 @@ ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_
   hipGraphExec_t ex = nullptr;
   HIPCHK(ls_graph(S, tu, gA, gC, ce, true, ps, &ex));
   const int64_t max_replays = (opt.max_iter + ce - 1) / ce + 1;
-  // When at most kHandoff instances remain, each step still pays every kernel's launch
-  // and latency for a handful of assets (about 41 us per step against ~12 us for an
-  // iteration of the plain kernel), so the last ones finish on the plain kernel, warm
-  // started from their current iterate and primal weight.
-  constexpr int64_t kHandoff = 4;
   int64_t replays = 0;
   bool handoff = false;
   hipError_t le = hipSuccess;
@@ -888,21 +924,11 @@ ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_
       const int64_t b = hact[j], o = offs[b], nb = n_b[b];
       const ffo::LsInst I = hinst[b];
       if (ffo::ls_launch_export(S, (int)b, (int)nb, D(ohw), D(ohy), ps)) return fail(FFO_EDEVICE, "export launch failed");
-      if (m > 0)
-        HIPCHK(hipMemcpy2DAsync(D(ohA), (size_t)nb * 8, A, (size_t)n_max * 8, (size_t)nb * 8, (size_t)m,
-                                hipMemcpyDeviceToDevice, ps));
-      ffo_options o2 = opt;
-      o2.max_iter = std::max<int64_t>(1, opt.max_iter - I.it);
-      o2.workgroups = 0;
-      o2.verbose = 0;
       ffo_info ib{};
-      const ffo_status sb = solve_impl(nb, k, m, 0, alpha + o, F, Omega, delta, s + o, q + o, d, D(ohA),
-                                       m ? L + (size_t)b * m : nullptr, m ? U + (size_t)b * m : nullptr, w0 + o, GMV,
-                                       lambda1, lambda2, lambda3, nullptr, D(ohw), D(ohy), I.omega, &o2, ps,
-                                       w_out + o, nullptr, &ib, nullptr);
-      if (sb == FFO_EINVAL || sb == FFO_ENOMEM || sb == FFO_EDEVICE) return sb;
-      ib.iters += I.it;
-      ib.restarts += I.restarts;
+      if (ffo_status sb = finish_plain(b, nb, o, n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d, GMV, lambda1,
+                                       lambda2, lambda3, opt, D(ohw), D(ohy), I.omega, I.it, I.restarts, D(ohA), ps,
+                                       w_out, &ib))
+        return sb;
       handed.emplace_back(b, ib);
     }
   }
@@ -916,10 +942,6 @@ ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_
   hipEventElapsedTime(&ms_setup, ws->ev[0], ws->ev[1]);
   hipEventElapsedTime(&ms_iter, ws->ev[1], ws->ev[2]);
   ffo_status worst = FFO_OK;
-  auto rank = [](ffo_status x) {
-    return x == FFO_EDEVICE ? 5 : x == FFO_NUMERIC ? 4 : x == FFO_INFEASIBLE ? 3 : x == FFO_TIMEOUT ? 2
-           : x == FFO_NOT_CONVERGED ? 1 : 0;
-  };
   for (int64_t b = 0; b < B; ++b) {
     const ffo_status st = status_of(hstat[b]);
     fill_info(&infos[b], st, hinfo + (size_t)b * ffo::INFO_LEN, ms_setup, ms_iter);
@@ -930,7 +952,7 @@ ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_
     infos[h.first].ms_iter = ms_iter;
   }
   for (int64_t b = 0; b < B; ++b)
-    if (rank((ffo_status)infos[b].status) > rank(worst)) worst = (ffo_status)infos[b].status;
+    worst = worse(worst, (ffo_status)infos[b].status);
   if (opt.verbose) {
     double passes = 0.0, iters = 0.0, pmax = 0.0;
     for (int64_t b = 0; b < B; ++b) {
@@ -1134,14 +1156,10 @@ size_t reg_bar_words(const RegTeams& t, int64_t b) { return reg_xgroups(t.g[b]) 
 ffo_status collect_teams(int64_t B, const int64_t* n_b, const double* hinfo, const int32_t* hstat, float ms_setup,
                          float ms_iter, const ffo::DevControl* hCt, int verbose, ffo_info* infos) {
   ffo_status worst = FFO_OK;
-  auto rank = [](ffo_status x) {
-    return x == FFO_EDEVICE ? 5 : x == FFO_NUMERIC ? 4 : x == FFO_INFEASIBLE ? 3 : x == FFO_TIMEOUT ? 2
-           : x == FFO_NOT_CONVERGED ? 1 : 0;
-  };
   for (int64_t b = 0; b < B; ++b) {
     const ffo_status st = status_of(hstat[b]);
     fill_info(&infos[b], st, hinfo + (size_t)b * ffo::INFO_LEN, ms_setup, ms_iter);
-    if (rank(st) > rank(worst)) worst = st;
+    worst = worse(worst, st);
   }
   if (verbose) {
     int64_t slow = 0;
@@ -1522,28 +1540,36 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     return fail(FFO_EINVAL, "ffo_solve_batched takes FFO_FP64, FFO_FP32 or FFO_FP32_BF16K");
   if (opt.batched_form < 0 || opt.batched_form > 2) return fail(FFO_EINVAL, "batched_form must be 0, 1 or 2");
   if (opt.autotune < -1 || opt.autotune > 1) return fail(FFO_EINVAL, "autotune must be -1, 0 or 1");
+  bool lockstep = false;
   {
     const bool ls_ok = opt.precision == FFO_FP64 && m + k >= 1 && m + k <= 160 && B <= 65536 && n_max <= (1 << 22);
     if (opt.batched_form == 2 && !ls_ok)
       return fail(FFO_EINVAL, "the lockstep batched form needs FFO_FP64, 1 <= m + k <= 160, B <= 65536 and "
                               "n_max <= 2^22");
-    if (opt.batched_form == 2 || (opt.batched_form == 0 && ls_ok))
-      return batched_lockstep(B, n_b, n_max, k, m, F, Omega, delta, A, offs, alpha, s, q, w0, L, U, d, GMV, lambda1,
-                              lambda2, lambda3, opt, stream, w_out, infos);
+    lockstep = opt.batched_form == 2 || (opt.batched_form == 0 && ls_ok);
   }
-
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   hipDeviceProp_t prop;
   HIPCHK(hipGetDeviceProperties(&prop, dev));
+  const int cus = std::max(1, prop.multiProcessorCount);
+  const int nr = (int)(m + k);
+  const int prec = opt.precision == FFO_FP32 ? ffo::PREC_FP32
+                   : (opt.precision == FFO_FP32_BF16K ? ffo::PREC_BF16K : ffo::PREC_FP64);
+  // The row-register teams where they apply; unless a form is asked for they also stand in
+  // for the lockstep form, with its results (256 instances, n 500 to 8000, 70 rows: 385 ms
+  // in lockstep, 206 here).  deterministic keeps the lockstep form, whose sums have a
+  // fixed order.
+  RegTeams rt;
+  const bool reg = opt.batched_form != 2 && !(lockstep && opt.deterministic) && plan_reg_teams(B, n_b, nr, 0, prec, d, opt, cus, &rt);
+  const bool as_lockstep = lockstep && reg;
+  if (lockstep && !reg)
+    return batched_lockstep(B, n_b, n_max, k, m, F, Omega, delta, A, offs, alpha, s, q, w0, L, U, d, GMV, lambda1,
+                            lambda2, lambda3, opt, stream, w_out, infos);
   int wall_khz = 0;
   if (hipDeviceGetAttribute(&wall_khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || wall_khz <= 0)
     wall_khz = 100000;
-  const int cus = std::max(1, prop.multiProcessorCount);
-  const int nr = (int)(m + k);
   const int ldk = (int)((n_max + 63) / 64 * 64);
-  const int prec = opt.precision == FFO_FP32 ? ffo::PREC_FP32
-                   : (opt.precision == FFO_FP32_BF16K ? ffo::PREC_BF16K : ffo::PREC_FP64);
 
   // ---- control and team sizing ----
   ffo::DevProblem p0{};
@@ -1555,6 +1581,10 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   c0.npow = 40; c0.verbose = opt.verbose; c0.spin_limit = 1u << 26; c0.wall_hz = (double)wall_khz * 1e3;
   c0.prec = prec; c0.spec = 1; c0.lds_k = 0; c0.lds_state = 0; c0.infeas = opt.infeasibility_check ? 1 : 0;
   c0.vmax = ffo::solve_vmax(p0);
+  if (as_lockstep) {   // the lockstep form tests no infeasibility and stops at checks only
+    c0.infeas = 0;
+    c0.max_iter = (opt.max_iter + opt.check_every - 1) / opt.check_every * opt.check_every;
+  }
   const int NW_MAX = 2048;   // assets per workgroup at most (bounds the LDS staging)
   // extra workgroups only while a team keeps at least this many assets each (ten n = 5000
   // instances: 25 workgroups per team at 128, 0.28 s per batch, against 19 and 0.34 s at 256)
@@ -1573,8 +1603,6 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const int W = occ * cus;
   // instances in decreasing size, cut into launches whose minimal teams fit the resident grid
   const TeamPlan tp = plan_teams(B, n_b, W, NW_MAX, NW_MIN);
-  RegTeams rt;
-  const bool reg = plan_reg_teams(B, n_b, nr, 0, prec, d, opt, cus, &rt);
   const std::vector<int>& g = reg ? rt.g : tp.g;
   const auto& chunks = tp.chunks;
 
@@ -1601,6 +1629,10 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t oP = carve(B, sizeof(ffo::DevProblem)), oS = carve(B, sizeof(ffo::DevState));
   const size_t nslot = std::max<size_t>(W, rt.inst.size());
   const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(nslot, 4), orank = carve(nslot, 4), onext = carve(1, 4);
+  // the hand-off of the last instances: their iterates and one copy of exposure rows
+  const int64_t hand = as_lockstep && B > kHandoff ? kHandoff : 0;
+  const size_t ohw = carve(hand ? (size_t)hand * n_max : 1, 8), ohy = carve(hand ? (size_t)hand * (nr + n_max) : 1, 8);
+  const size_t ohA = carve(hand ? (size_t)std::max<int64_t>(m, 1) * n_max : 1, 8);
   const size_t total = off;
   size_t hoff = 0;
   auto hcarve = [&](size_t bytes) { const size_t o = hoff; hoff = align_up(hoff + bytes); return o; };
@@ -1717,7 +1749,70 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
                  "state in LDS %d (2: registers), %zu bytes | setup %.3f ms solve %.3f ms\n",
                  (long long)B, reg ? 1 : chunks.size(), reg ? rt.grid : W, occ, lds_cap, reg ? 2 : ckl[0], reg ? 2 : csl[0],
                  reg ? 0 : clds[0], ms_setup, ms_iter);
-  return collect_teams(B, n_b, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
+  ffo_status worst = collect_teams(B, n_b, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
+  if (!hand || worst == FFO_EDEVICE) return worst;
+
+  // ---- the lockstep form's hand-off: there, at the first check that leaves at most
+  // kHandoff instances, these go on as warm-started plain solves.  That check is the
+  // iteration count of the (kHandoff + 1)-th longest solve.  The longer ones run again up to
+  // it (the same iterations, all of them side by side) and go on from there.
+  std::vector<int64_t> its(B);
+  for (int64_t b = 0; b < B; ++b) its[b] = infos[b].iters;
+  std::nth_element(its.begin(), its.begin() + kHandoff, its.end(), std::greater<int64_t>());
+  const int64_t at = its[kHandoff];
+  RegTeams ht;
+  ht.plan = rt.plan;
+  std::vector<int64_t> left;
+  for (size_t t = 0; t < rt.inst.size(); ++t) {
+    const int b = rt.inst[t];
+    if (infos[b].iters <= at) continue;
+    if (rt.rank[t] == 0) left.push_back(b);
+    ht.inst.push_back(b);
+    ht.rank.push_back(rt.rank[t]);
+  }
+  if (left.empty()) return worst;
+  ht.grid = (int)std::min<size_t>(ht.inst.size(), (size_t)cus);
+  for (size_t j = 0; j < left.size(); ++j) {
+    const int64_t b = left[j];
+    hS[b].w_out = D(ohw) + j * n_max;
+    hS[b].y_out = D(ohy) + j * (nr + n_max);
+    hCt[b].stop_at = at;
+    HIPCHK(fill(D(oxb) + xoff[b], (xoff[b + 1] - xoff[b]) * 8, 0u, hs));
+    HIPCHK(fill(D(obar) + boff[b], (boff[b + 1] - boff[b]) * 8, 0u, hs));
+  }
+  HIPCHK(fill(Bd + onext, 4, 0u, hs));
+  HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
+  HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
+  if (ffo_status st = launch_reg_teams(ht, Bd + oP, Bd + oS, Bd + oCt, Bd + oteam, Bd + orank, Bd + onext, Hb + hteam_o,
+                                       Hb + hrank_o, stream))
+    return st;
+  HIPCHK(hipMemcpyAsync(hinfo, Bd + oinfo, (size_t)B * ffo::INFO_LEN * 8, hipMemcpyDeviceToHost, hs));
+  HIPCHK(hipMemcpyAsync(hstat, Bd + ostat, (size_t)B * 4, hipMemcpyDeviceToHost, hs));
+  HIPCHK(hipStreamSynchronize(hs));
+  for (size_t j = 0; j < left.size(); ++j) {
+    const int64_t b = left[j];
+    const double* h = hinfo + (size_t)b * ffo::INFO_LEN;
+    if (hstat[b] != ffo::DS_NOT_CONVERGED || (int64_t)h[ffo::IX_ITERS] != at)
+      return fail(FFO_EDEVICE, "a team ended without a result (bounded wait expired)");
+    if (ffo_status st = finish_plain(b, n_b[b], offs[b], n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d, GMV,
+                                     lambda1, lambda2, lambda3, opt, D(ohw) + j * n_max, D(ohy) + j * (nr + n_max),
+                                     h[ffo::IX_OMEGA], at, (int64_t)h[ffo::IX_RESTARTS], D(ohA), hs, w_out, &infos[b]))
+      return st;
+  }
+  HIPCHK(hipEventRecord(ws->ev[2], hs));
+  HIPCHK(hipEventSynchronize(ws->ev[2]));
+  hipEventElapsedTime(&ms_iter, ws->ev[1], ws->ev[2]);
+  worst = FFO_OK;
+  for (int64_t b = 0; b < B; ++b) {
+    infos[b].ms_setup = ms_setup;
+    infos[b].ms_iter = ms_iter;
+    worst = worse(worst, (ffo_status)infos[b].status);
+  }
+  g_err = worst == FFO_OK ? "" : worst == FFO_INFEASIBLE ? "at least one instance is infeasible"
+          : worst == FFO_NOT_CONVERGED ? "iteration limit reached for at least one instance"
+          : worst == FFO_TIMEOUT ? "time limit reached for at least one instance"
+                                 : "NaN or Inf in an FP64 check of at least one instance";
+  return worst;
 }
 
 ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int64_t T, const double* const* alpha,

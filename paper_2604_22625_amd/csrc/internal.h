@@ -83,6 +83,8 @@ struct DevControl {
   int32_t infeas;       // 1: test the exposure-dual displacement for an infeasibility certificate
   double omega0;        // starting primal weight (> 0)
   int32_t xgroups;      // atomic exchange: copies of the slot (workgroup w adds into copy w % xgroups)
+  int64_t stop_at;      // row-register kernel: > 0 stops after that many iterations (a multiple of
+                        // check_every) and writes the iterate itself, not T(z), to w_out and y_out
 };
 
 // Breakpoint lists: per workgroup and period, a count and LIST_CAP entries

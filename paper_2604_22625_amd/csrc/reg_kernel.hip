@@ -836,6 +836,19 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
         }
         ++it;
         __syncthreads();
+        if (check && it == cp->stop_at) {   // hand the iterate over, unscaled, as a warm start
+          const auto [tid, lane, wave, rg, slot, li, val, mine, rown] = place<CA>(tid0, nwa, nr);
+          const DevState& s = *opaque(sp);
+          if (mine) { s.w_out[i0 + li] = dc * x; s.y_out[nr + i0 + li] = yc; }
+          if (wg == 0 && rown) s.y_out[tid] = L.dr[tid] * L.y[tid];
+          if (wg == 0 && tid == 0) {
+            s.info[IX_ITERS] = (double)it;
+            s.info[IX_RESTARTS] = (double)L.restarts;
+            s.info[IX_OMEGA] = omega;
+            s.status[0] = DS_NOT_CONVERGED;
+          }
+          return;
+        }
       }
     }
   }

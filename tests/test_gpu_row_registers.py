@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 from oracle.problem import kkt, normalize
-from synth import make_single
+from synth import make_batch, make_single
 
 pytestmark = pytest.mark.gpu
 
@@ -96,3 +96,19 @@ def test_many_markets_share_the_queue():
         W, i = ff.solve_instance(insts[j], tol=TOL, time_limit_s=20.0, max_iter=100_000)
         assert infos[j].status == 0 and infos[j].iters == i.iters
         assert float((W - Ws[j]).abs().max()) <= 1e-10 * float(W.abs().max())
+
+
+@pytest.mark.parametrize("B,cut", [(4, 100_000), (5, 100_000), (12, 100_000), (12, 700), (12, 1000)])
+def test_default_batch_keeps_the_lockstep_results(B, cut):
+    """The default batched form against the lockstep form asked for by name: the same
+    iterations, restarts and statuses (the hand-off of the last instances and the iteration
+    limit at a check included), the weights within rounding."""
+    ff = _gpu()
+    batch = make_batch(B, 10, 8, seed=B, n_lo=100, n_hi=900)
+    print(f"[case] batch {B} {cut}", flush=True)
+    kw = dict(tol=TOL, time_limit_s=20.0, max_iter=cut, raise_on_failure=False)
+    W, a = ff.solve_batched(batch, **kw)
+    Wl, b = ff.solve_batched(batch, form="lockstep", **kw)
+    torch.cuda.synchronize()
+    assert [(i.status, i.iters, i.restarts) for i in a] == [(i.status, i.iters, i.restarts) for i in b]
+    assert float((W - Wl).abs().max()) <= 1e-10 * float(Wl.abs().max())
