@@ -308,9 +308,11 @@ hipError_t fill(void* p, size_t bytes, uint32_t value, hipStream_t hs) {
   return hipGetLastError();
 }
 
-// Copies of the exchange slot for a team of the row-register kernel (fewer, larger
-// workgroups): the same trade, one copy per about 16 workgroups.
-int reg_xgroups(int nwg) { return nwg <= 20 ? 1 : nwg <= 40 ? 2 : nwg <= 80 ? 4 : ffo::XG_MAX; }
+// Copies of the exchange slot for a team of the row-register kernels (fewer, larger
+// workgroups): the same trade.  Per iteration with 1, 2, 4 and 8 copies: 32 workgroups
+// (T = 10, 80 rows) 16.5, 17.3, 17.2, 19.0 us; 47 (T = 20, 100 rows) 26.7, 26.5, 27.1, 29.1;
+// 47 (T = 10, 22 rows) 12.6, 11.7, 11.8, 12.5.
+int reg_xgroups(int nwg) { return nwg <= 40 ? 1 : nwg <= 80 ? 2 : nwg <= 128 ? 4 : ffo::XG_MAX; }
 
 // Finite-value check of an optional caller array (warm-start data); sets `bit` in flag.
 __global__ void k_check_finite(const double* x, int64_t cnt, int bit, int* flag) {
@@ -425,6 +427,12 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   ffo::RegPlan rp{};
   const bool reg = T == 0 && c.prec == ffo::PREC_FP64 && !opt.deterministic && opt.workgroups == 0 && c.spec &&
                    opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::reg_plan(n, nr, cus, &rp);
+  // The same for multi-period solves of up to 31 periods and 112 rows.  Per iteration there
+  // and here: T = 20, n = 3000, 100 rows 67.5 and 26.5 us; T = 10, n = 2000, 80 rows 31.9 and
+  // 16.5; T = 10, n = 3000, 22 rows 21.9 and 11.7; T = 5, n = 50, 8 rows 14.7 and 4.9.
+  ffo::MpPlan mp{};
+  const bool mpk = T > 0 && c.prec == ffo::PREC_FP64 && !opt.deterministic && opt.workgroups == 0 && opt.speculative <= 0 &&
+                   opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::mp_plan(n, nr, (int)P, cus, lds_cap, &mp);
   // ---- workspace layout (one for both kernels) ----
   const size_t Pn = (size_t)P * n, Tpn = (size_t)Tp * n;
   size_t off = 0;
@@ -522,13 +530,13 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   HIPCHK(fill(B + obar, 8 * ffo::BAR_WORDS, 0u, hs));
   HIPCHK(fill(B + oinfo, ffo::INFO_LEN * 8, 0u, hs));
   HIPCHK(fill(B + ostat, 4, 0xffffffffu, hs));
-  if (reg) {
+  if (reg || mpk) {
     // the kernel reads its records from the (otherwise unused) state arrays
     static_assert(sizeof(p) <= 256 && sizeof(sv) <= 256 && sizeof(c) <= 256, "one record per state array");
-    c.nwg = nwg = rp.nwg;
+    c.nwg = nwg = reg ? rp.nwg : mp.nwg;
     c.nw = nw = (int)((n + nwg - 1) / nwg);
     c.xgroups = reg_xgroups(nwg);
-    c.vmax = ffo::reg_vmax(rp.ra);
+    c.vmax = reg ? ffo::reg_vmax(rp.ra) : mp.vmax;
     char* hR = H + hR_o;
     std::memcpy(hR, &p, sizeof(p));
     std::memcpy(hR + 256, &sv, sizeof(sv));
@@ -540,6 +548,8 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   if (ev) HIPCHK(hipEventRecord(ev[1], hs));
   if (int e = reg ? ffo::launch_reg(rp, (const ffo::DevProblem*)(B + ost[0]), (const ffo::DevState*)(B + ost[1]),
                                     (const ffo::DevControl*)(B + ost[2]), stream)
+              : mpk ? ffo::launch_mp(mp, (const ffo::DevProblem*)(B + ost[0]), (const ffo::DevState*)(B + ost[1]),
+                                     (const ffo::DevControl*)(B + ost[2]), stream)
                   : ffo::launch_solve(p, sv, c, stream, lds))
     return fail(FFO_EDEVICE, std::string("cooperative launch of the solve kernel failed: ") +
                                  hipGetErrorString((hipError_t)e));

@@ -157,6 +157,16 @@ int launch_reg(const RegPlan& plan, const DevProblem* dp, const DevState* ds, co
 int launch_reg_queue(const RegPlan& plan, const DevProblem* dp, const DevState* ds, const DevControl* dc, const int* inst,
                      const int* rank, int tickets, int* next, int grid, void* stream);
 
+// Multi-period FP64 solve with the constraint rows in registers (mp_kernel.hip): jt periods
+// per wave, nrt tiles of 16 rows, 64 assets per workgroup.  mp_plan returns false where the
+// periods (more than 31), the rows (more than 112), the assets or the LDS do not fit.
+struct MpPlan {
+  int jt, nrt, nwg, vmax;
+  size_t lds;
+};
+bool mp_plan(int64_t n, int nr, int P, int cus, size_t lds_cap, MpPlan* out);
+int launch_mp(const MpPlan& plan, const DevProblem* dp, const DevState* ds, const DevControl* dc, void* stream);
+
 // Setup kernels (setup_kernels.hip).
 // Batched form: shared rows K diag(dc) of the n_max-asset universe (unscaled by rows),
 // per-instance row scales drs [B][nr] over each prefix of nb[b] columns (nb on the

@@ -26,7 +26,7 @@
 #include <stdint.h>
 #include <algorithm>
 #include "internal.h"
-#include "cost_math.h"
+#include "team_exchange.h"
 #include "wave_ops.h"
 
 namespace ffo {
@@ -54,39 +54,6 @@ struct RegLds {
   int ok, restarts, checks, miss, miss_in, miss_out, rounds;
 };
 
-__device__ __forceinline__ int wave_of(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
-
-// The thread index, opaque to the compiler: addresses and masks made from it stay in the
-// block that uses them (hoisted out of the iteration they would take registers from the rows).
-__device__ __forceinline__ int fresh(int tid) {
-  asm volatile("" : "+v"(tid));
-  return tid;
-}
-
-// A value that is the same in every lane, as a scalar register pair.
-__device__ __forceinline__ double uni(double x) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
-  return u2d((unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u),
-             (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32)));
-}
-
-template <class T>
-using gptr = __attribute__((address_space(1))) T*;   // loads through it count against vmcnt only
-template <class T>
-__device__ __forceinline__ gptr<T> glob(T* q) { return (gptr<T>)q; }
-
-// Exchange state of one workgroup (the protocol of solve_kernel.hip's atomic mode:
-// grouped copies of a triple-buffered slot, two-level counter barrier, bounded waits).
-struct RegX {
-  gptr<double> xbuf;
-  gptr<unsigned long long> bar;
-  uint32_t epoch;                        // exchanges done (2^32 of them take hours)
-  int at;                                // epoch % 3: slot of the next exchange
-  int nwg, wg, ng, grp, gsize, vmax;
-  int zper;                              // words that this workgroup clears
-  uint32_t spin_limit;
-};
-
 // Sum over the waves of partial sum j (mx: the maximum for j = 1), in wave order.
 template <int RA, int CA>
 __device__ __forceinline__ double wave_parts(const RegLds<RA, CA>& L, int j, bool mx) {
@@ -109,73 +76,21 @@ __device__ __forceinline__ bool exchange_begin(RegX& X, RegLds<RA, CA>& L, int t
                                                uint32_t spin_limit) {
   __syncthreads();   // every wave's partial sums are in part
   if (X.nwg == 1) return true;
-  gptr<double> cur = X.xbuf + (size_t)(X.at * X.ng * X.vmax);
   if (tid < V) {
     const double s = wave_parts(L, tid, mx);
-    gptr<double> a = cur + (size_t)X.grp * X.vmax + tid;
-    if (mx && tid == 1)   // bit patterns order non-negative doubles like their values
-      __hip_atomic_fetch_max((gptr<unsigned long long>)a, (unsigned long long)__double_as_longlong(s), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-    else if (s != 0.0)
-      __hip_atomic_fetch_add(a, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (mx && tid == 1) team_max(X, tid, s);
+    else team_add(X, tid, s);
   }
-  __builtin_amdgcn_s_waitcnt(0);   // this wave's atomics and clears are complete
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long target;
-    gptr<unsigned long long> poll = X.bar;
-    if (X.ng > 1) {
-      target = X.epoch + 1ull;
-      const unsigned long long gt = (X.epoch + 1ull) * (unsigned long long)X.gsize;
-      if (__hip_atomic_fetch_add(X.bar + XGSTRIDE * (1 + X.grp), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gt) {
-        if (__hip_atomic_fetch_add(X.bar, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
-            (X.epoch + 1ull) * (unsigned long long)X.ng)
-          for (int g = 0; g < X.ng; ++g)
-            __hip_atomic_store(X.bar + XGSTRIDE * (1 + XG_MAX + g), X.epoch + 1ull, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-      }
-      poll = X.bar + XGSTRIDE * (1 + XG_MAX + X.grp);
-    } else {
-      target = (X.epoch + 1ull) * (unsigned long long)X.nwg;
-      __hip_atomic_fetch_add(X.bar, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    uint32_t spins = 0;
-    int ok = 1;
-    while (__hip_atomic_load(poll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (++spins > 64) __builtin_amdgcn_s_sleep(1);
-      if (spins >= spin_limit) { ok = 0; break; }
-    }
-    L.ok = ok;
-  }
-  __syncthreads();
-  return __builtin_amdgcn_readfirstlane(L.ok) != 0;
+  return team_barrier(X, tid, &L.ok, spin_limit);
 }
 
 template <int RA, int CA>
 __device__ __forceinline__ double total(const RegX& X, const RegLds<RA, CA>& L, int j, bool mx) {
-  if (X.nwg == 1) return wave_parts(L, j, mx);
-  gptr<double> cur = X.xbuf + (size_t)(X.at * X.ng * X.vmax) + j;
-  if (X.ng == 1) return __hip_atomic_load(cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  double u[XG_MAX];   // the copies combine in a fixed order, every load issued before the first use
-#pragma unroll
-  for (int g = 0; g < XG_MAX; ++g)
-    u[g] = g < X.ng ? __hip_atomic_load(cur + g * X.vmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
-  double t = u[0];
-  const bool m = mx && j == 1;
-#pragma unroll
-  for (int g = 1; g < XG_MAX; ++g) t = m ? fmax(t, u[g]) : t + u[g];
-  return t;
+  return X.nwg == 1 ? wave_parts(L, j, mx) : team_total(X, j, mx && j == 1);
 }
 
-// Clears the slot used two exchanges from now (its last readers passed this barrier).
 __device__ __forceinline__ void exchange_end(RegX& X, int tid) {
-  if (X.nwg == 1) return;
-  gptr<double> z = X.xbuf + (size_t)((X.at == 0 ? 2 : X.at - 1) * X.ng * X.vmax);
-  const int zl = X.ng * X.vmax;
-  for (int j = X.wg * X.zper + tid; j < min(zl, (X.wg + 1) * X.zper); j += NT)
-    __hip_atomic_store(z + j, 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  X.epoch++;
-  X.at = X.at == 2 ? 0 : X.at + 1;
+  if (X.nwg > 1) team_end(X, tid, NT);
 }
 
 // The whole exchange, totals to LDS.
@@ -290,25 +205,6 @@ __device__ __forceinline__ void stats(const double* ab, const double* ia, double
   if (lane == 0) { out[0] = S0; out[1] = mx; }
 }
 
-// 1 / x and sqrt(x) by Newton steps on the hardware's estimates (x normal and positive;
-// within 1 ulp, without the scaling of subnormal and huge operands that the library's have).
-__device__ __forceinline__ double recip(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
-}
-__device__ __forceinline__ double root(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-  double e = fma(-g, h, 0.5);
-  g = fma(g, e, g);
-  h = fma(h, e, h);
-  e = fma(-g, h, 0.5);
-  g = fma(g, e, g);
-  h = fma(h, e, h);
-  return fma(fma(-g, g, x), h, g);
-}
-
 // The bracket decision of solve_kernel.hip (bracket_decide) from statistic `lane` in each
 // lane; uniform result (1 = exact from the central pair, 4 = exact from another interval
 // without breakpoints, 2 = zero, 0 / 3 = multisection on [lo, hi]).
@@ -375,12 +271,6 @@ __device__ __forceinline__ bool multisect(RegX& X, RegLds<RA, CA>& L, double lo,
   return true;
 }
 
-__device__ __forceinline__ void predict(double mu, double mprev, double w, double& cen, double& hw) {
-  if (mu <= 0.0) { cen = 0.0; hw = 0.0; return; }
-  cen = uni(fmax(mu + (mu - mprev), 0.5 * mu));
-  hw = uni(w * mu);
-}
-
 // Sum of each thread's NV values over the workgroup (fixed order), for every thread.
 template <int NV, int RA, int CA>
 __device__ __forceinline__ void wg_total(RegLds<RA, CA>& L, double (&v)[NV], int tid) {
@@ -400,37 +290,6 @@ __device__ __forceinline__ void wg_total(RegLds<RA, CA>& L, double (&v)[NV], int
     v[q] = t;
   }
   __syncthreads();
-}
-
-// The same pointer, opaque to the compiler: loads through it stay where they are written
-// (hoisted out of the iteration, the fields that only a check needs would take registers
-// from the rows).
-template <class T>
-__device__ __forceinline__ const T* opaque(const T* q) {
-  asm volatile("" : "+s"(q));
-  return q;
-}
-
-// Conjugate of the trade cost at e (conj_cost of cost_math.h for d = 3/2 and d = 2).
-__device__ __forceinline__ double conj15(double e, double a, double b, double d) {
-  const double r = fabs(e) - a;
-  if (r <= 0.0) return 0.0;
-  if (b <= 0.0) return INFINITY;
-  const double t = r / (b * d);
-  return d == 2.0 ? 0.5 * r * t : r * t * t / 3.0;
-}
-
-// prox_cost of cost_math.h for d = 3/2 and d = 2, with the step times a and b given.
-__device__ __forceinline__ double prox15(double z, double ta, double tb, double d) {
-  const double r = fmax(fabs(z) - ta, 0.0);
-  double t;
-  if (d == 2.0) {
-    t = r / (1.0 + 2.0 * tb);
-  } else {
-    const double c = 1.5 * tb, u = 2.0 * r * recip(c + root(fmax(fma(c, c, 4.0 * r), 1e-280)));
-    t = u * u;
-  }
-  return r <= 0.0 ? 0.0 : (z > 0.0 ? t : -t);
 }
 
 // A thread's place: its wave and lane, the row of lanes' asset `slot` among the wave's and
@@ -468,14 +327,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
   const int i0 = wg * ctl.nw, nwa = max(0, min(ctl.nw, n - i0));
   const double rho = ctl.rho, d = p.d, g1 = p.g1;
 
-  RegX X;
-  X.xbuf = glob(s.xbuf); X.bar = glob(s.bar); X.epoch = 0; X.at = 0; X.nwg = nwg; X.wg = wg;
-  X.ng = max(1, min(ctl.xgroups, min(XG_MAX, nwg)));
-  X.grp = wg % X.ng;
-  X.gsize = (nwg - X.grp + X.ng - 1) / X.ng;
-  X.vmax = ctl.vmax;
-  X.zper = (X.ng * X.vmax + nwg - 1) / nwg;
-  X.spin_limit = ctl.spin_limit;
+  RegX X = team_init(s, ctl, wg);
 
   double K[RA][CA];
   double x, yc, tx, ty, dc;   // the owned asset: iterates, their images, column scale
