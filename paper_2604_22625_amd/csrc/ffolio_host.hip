@@ -1321,12 +1321,7 @@ ffo_status ffo_risk_model(int64_t days, int64_t n, int64_t p, const double* R, c
   if (p < 1 || p > 8) return fail(FFO_EINVAL, "p must lie in [1, 8]");
   if (min_obs < 0 || min_obs > days) return fail(FFO_EINVAL, "min_obs must lie in [0, days]");
   if (!R || !Fr || !beta || !Sigma_f || !D || !valid) return fail(FFO_EINVAL, "null array pointer");
-  int dev = 0;
-  HIPCHK(hipGetDevice(&dev));
-  Workspace* ws = nullptr;
-  if (ffo_status st = get_workspace(dev, stream, ffo::rm_workspace_bytes(days, n, p), 256, &ws, 4)) return st;
-  if (ffo::launch_risk_model((int)days, (int)n, (int)p, R, Fr, mask, (int)min_obs, (double*)ws->base, beta, Sigma_f,
-                             D, valid, stream))
+  if (ffo::launch_risk_model((int)days, (int)n, (int)p, R, Fr, mask, (int)min_obs, beta, Sigma_f, D, valid, stream))
     return fail(FFO_EDEVICE, "risk-model kernel launch failed");
   HIPCHK(hipStreamSynchronize((hipStream_t)stream));
   return FFO_OK;

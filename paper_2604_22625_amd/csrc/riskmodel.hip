@@ -5,26 +5,38 @@
 // factor covariance Sigma_f (centred, 1/(days-1)) and the specific variances D_ii (the
 // centred sample variance of the residuals over the observed days).
 //
-// The work is one pass over R, which dominates the bytes (days x n doubles), so the
-// kernels are laid out for streaming it: lanes run over 64 consecutive assets (every
-// load of a day's returns is one 512-byte coalesced row segment), the four waves of a
-// workgroup take interleaved days of a 64-day chunk, and a grid over (asset block, day
-// chunk) keeps every compute unit busy.  Each asset has its own Gram matrix (the mask
-// selects its days), so this is a batch of small normal-equation systems, not a GEMM:
-// per asset the pass accumulates the p(p+1)/2 Gram entries, the p cross products, the
-// sum and sum of squares of its returns, its observation count and the p factor sums;
-// a second kernel adds the day chunks in order, solves the p x p system by Cholesky and
-// forms D from the sums (sum theta^2 = sum r^2 - 2 beta^T c + beta^T G beta).
+// Each asset has its own Gram matrix (the mask selects its days), so this is a batch of
+// small normal-equation systems: per asset one pass over its returns accumulates the
+// p(p+1)/2 Gram entries, the p cross products, the sum and sum of squares of its returns,
+// its observation count and the p factor sums; a Cholesky factorisation solves the p x p
+// system, and D follows from the sums (sum theta^2 = sum r^2 - 2 beta^T c + beta^T G beta).
+//
+// One launch: a workgroup takes 16 assets (a day's returns of them are one 128-byte
+// segment) and all days, 16 threads an asset; their sums meet in LDS, where 16 threads
+// solve the systems.  One more workgroup forms Sigma_f beside them.
+//
+// What bounds it: latency, of the loads (32 days a thread in eight steps, one step ahead) and of
+// the solve's divisions (3.4 us).  504 days x 5000 assets, p = 6, masked: 18 us, against 49 in
+// three launches with the partial sums of each 64 days in device memory; the call 71 -> 43 us.
+// 512 threads a workgroup (one per compute unit) take 19 us, 128 threads 27; with the sums
+// held to 128 registers they spill and it takes 39.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <algorithm>
 #include <cmath>
 #include "internal.h"
+#include "wave_ops.h"
 
 namespace ffo {
 namespace {
 
-constexpr int RM_CHUNK = 64;   // days per partial-sum tile
+constexpr int RM_NT = 256, RM_W = RM_NT / 64;   // threads and waves of a workgroup
+constexpr int RM_TILE = 16;                     // assets of a workgroup
+constexpr int RM_GROUPS = RM_NT / RM_TILE;      // threads per asset
+constexpr int RM_CHUNK = 512;                   // days of factor returns in LDS at a time
+constexpr int RM_U = 4;                         // days of a thread per step, and in flight
+constexpr int RM_XCDS = 8;
+static_assert(RM_CHUNK % (RM_U * RM_GROUPS) == 0, "a step stays in its chunk");
 
 template <int P>
 struct RmDim {
@@ -33,147 +45,72 @@ struct RmDim {
 };
 
 template <int P>
-__global__ __launch_bounds__(256) void k_rm_partial(int days, int n, const double* __restrict__ R,
-                                                    const double* __restrict__ Fr, const uint8_t* __restrict__ mask,
-                                                    double* __restrict__ part) {
-  constexpr int NV = RmDim<P>::NV, G = RmDim<P>::G;
-  __shared__ double fs[RM_CHUNK * P];
-  __shared__ double red[4 * NV * 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = blockIdx.x * 64 + lane;
-  const int k0 = blockIdx.y * RM_CHUNK, k1 = min(days, k0 + RM_CHUNK);
-  for (int e = threadIdx.x; e < (k1 - k0) * P; e += blockDim.x) fs[e] = Fr[(size_t)k0 * P + e];
-  __syncthreads();
-  double acc[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-  const bool col = i < n;
-  for (int k = k0 + wave; k < k1; k += 16) {   // four days per step, loads first
-    double rv[4];
-    bool ob[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int kk = k + 4 * u;
-      const bool in = col && kk < k1;
-      ob[u] = in && (mask == nullptr || mask[(size_t)kk * n + i] != 0);
-      rv[u] = ob[u] ? R[(size_t)kk * n + i] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (!ob[u]) continue;
-      const double* f = fs + (k + 4 * u - k0) * P;
-      const double r = rv[u];
-      int g = 0;
-#pragma unroll
-      for (int a = 0; a < P; ++a)
-#pragma unroll
-        for (int b = a; b < P; ++b) { acc[g] = fma(f[a], f[b], acc[g]); ++g; }
-#pragma unroll
-      for (int a = 0; a < P; ++a) acc[G + a] = fma(f[a], r, acc[G + a]);
-      acc[G + P] += r;
-      acc[G + P + 1] = fma(r, r, acc[G + P + 1]);
-      acc[G + P + 2] += 1.0;
-#pragma unroll
-      for (int a = 0; a < P; ++a) acc[G + P + 3 + a] += f[a];
-    }
-  }
-  // the four waves' sums, added in wave order
-#pragma unroll
-  for (int v = 0; v < NV; ++v) red[(wave * NV + v) * 64 + lane] = acc[v];
-  __syncthreads();
-  if (wave == 0 && col) {
-    double* out = part + (size_t)blockIdx.y * NV * n;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const double s = red[(0 * NV + v) * 64 + lane] + red[(1 * NV + v) * 64 + lane] +
-                       red[(2 * NV + v) * 64 + lane] + red[(3 * NV + v) * 64 + lane];
-      out[(size_t)v * n + i] = s;
-    }
-  }
-}
+union RmLds {
+  double fs[RM_CHUNK * P];                          // factor returns of a chunk of days
+  double red[(RM_W + 1) * RmDim<P>::NV * RM_TILE];  // the waves' sums, then the totals
+};
 
+// The p x p system and the residual variance of asset i from its sums in LDS, value v at
+// s[v * RM_TILE] (read where they are used: copies would take the registers that the sums need).
 template <int P>
-__global__ __launch_bounds__(256) void k_rm_solve(int n, int nchunk, int min_obs, const double* __restrict__ part,
-                                                  double* __restrict__ beta, double* __restrict__ D,
-                                                  int32_t* __restrict__ valid) {
-  constexpr int NV = RmDim<P>::NV, G = RmDim<P>::G;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double s[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) s[v] = 0.0;
-  for (int c = 0; c < nchunk; ++c) {
-    const double* pc = part + (size_t)c * NV * n;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] += pc[(size_t)v * n + i];
-  }
-  const double cnt = s[G + P + 2];
+__device__ __forceinline__ void solve_asset(const double* s, int min_obs, int i, double* __restrict__ beta,
+                                            double* __restrict__ D, int32_t* __restrict__ valid) {
+  constexpr int G = RmDim<P>::G;
+  const auto at = [&](int v) { return s[v * RM_TILE]; };
+  const auto tri = [](int r, int c) { return r * (r + 1) / 2 + c; };            // lower factor, row-major
+  const auto gram = [](int a, int b) { return a * P - a * (a - 1) / 2 + b - a; };   // entry (a, b), a <= b
+  const double cnt = at(G + P + 2);
   double b[P];
 #pragma unroll
   for (int a = 0; a < P; ++a) b[a] = 0.0;
   bool ok = cnt >= (double)min_obs && cnt >= (double)(P + 1);
   if (ok) {
-    // Cholesky of the Gram matrix (lower factor Lc, row-major), then two triangular solves
-    double A[P][P], Lc[P][P];
-    {
-      int g = 0;
-#pragma unroll
-      for (int a = 0; a < P; ++a)
-#pragma unroll
-        for (int c2 = a; c2 < P; ++c2) { A[a][c2] = s[g]; A[c2][a] = s[g]; ++g; }
-    }
-#pragma unroll
-    for (int a = 0; a < P; ++a)
-#pragma unroll
-      for (int c2 = 0; c2 < P; ++c2) Lc[a][c2] = 0.0;
+    // Cholesky of the Gram matrix, then two triangular solves
+    double Lc[G];
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-      double dj = A[j][j];
+      double dj = at(gram(j, j));
 #pragma unroll
-      for (int q = 0; q < j; ++q) dj -= Lc[j][q] * Lc[j][q];
+      for (int q = 0; q < j; ++q) dj -= Lc[tri(j, q)] * Lc[tri(j, q)];
       if (!(dj > 1e-300)) ok = false;
       const double rj = ok ? sqrt(dj) : 1.0;
-      Lc[j][j] = rj;
+      Lc[tri(j, j)] = rj;
 #pragma unroll
-      for (int r2 = j + 1; r2 < P; ++r2) {
-        double v = A[r2][j];
+      for (int r = j + 1; r < P; ++r) {
+        double v = at(gram(j, r));
 #pragma unroll
-        for (int q = 0; q < j; ++q) v -= Lc[r2][q] * Lc[j][q];
-        Lc[r2][j] = v / rj;
+        for (int q = 0; q < j; ++q) v -= Lc[tri(r, q)] * Lc[tri(j, q)];
+        Lc[tri(r, j)] = v / rj;
       }
     }
     if (ok) {
       double y[P];
 #pragma unroll
       for (int a = 0; a < P; ++a) {
-        double v = s[G + a];
+        double v = at(G + a);
 #pragma unroll
-        for (int q = 0; q < a; ++q) v -= Lc[a][q] * y[q];
-        y[a] = v / Lc[a][a];
+        for (int q = 0; q < a; ++q) v -= Lc[tri(a, q)] * y[q];
+        y[a] = v / Lc[tri(a, a)];
       }
 #pragma unroll
       for (int a = P - 1; a >= 0; --a) {
         double v = y[a];
 #pragma unroll
-        for (int q = a + 1; q < P; ++q) v -= Lc[q][a] * b[q];
-        b[a] = v / Lc[a][a];
+        for (int q = a + 1; q < P; ++q) v -= Lc[tri(q, a)] * b[q];
+        b[a] = v / Lc[tri(a, a)];
       }
-    } else {
-#pragma unroll
-      for (int a = 0; a < P; ++a) b[a] = 0.0;
     }
   }
   // residual sums: theta = r - beta^T f over the observed days
-  double st = s[G + P], st2 = s[G + P + 1];
+  double st = at(G + P), st2 = at(G + P + 1);
   if (ok) {
     double bc = 0.0, bGb = 0.0, bf = 0.0;
-    int g = 0;
 #pragma unroll
     for (int a = 0; a < P; ++a) {
-      bc = fma(b[a], s[G + a], bc);
-      bf = fma(b[a], s[G + P + 3 + a], bf);
+      bc = fma(b[a], at(G + a), bc);
+      bf = fma(b[a], at(G + P + 3 + a), bf);
 #pragma unroll
-      for (int c2 = a; c2 < P; ++c2) { bGb += (a == c2 ? 1.0 : 2.0) * b[a] * b[c2] * s[g]; ++g; }
+      for (int c = a; c < P; ++c) bGb += (a == c ? 1.0 : 2.0) * b[a] * b[c] * at(gram(a, c));
     }
     st -= bf;
     st2 = st2 - 2.0 * bc + bGb;
@@ -186,92 +123,176 @@ __global__ __launch_bounds__(256) void k_rm_solve(int n, int nchunk, int min_obs
   valid[i] = ok ? 1 : 0;
 }
 
-// Sigma_f = (Fr - mean)^T (Fr - mean) / (days - 1), one workgroup: each thread sums its
-// days for all P means (pass 1) and all P(P+1)/2 centred products (pass 2); one
-// fixed-order workgroup reduction per pass.
-template <int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double* red) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    double x = v[q];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    if (lane == 0) red[w * NV + q] = x;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NV; ++q) v[q] = red[q] + red[NV + q] + red[2 * NV + q] + red[3 * NV + q];
-  __syncthreads();
-}
-
+// Sigma_f = (Fr - mean)^T (Fr - mean) / (days - 1) by one workgroup, centred in a second pass
+// over the days: in each, wave w sums the entries w, w + RM_W, ... over the chunk in LDS.
 template <int P>
-__global__ __launch_bounds__(256) void k_rm_cov(int days, const double* __restrict__ Fr, double* __restrict__ Sf) {
-  constexpr int G = P * (P + 1) / 2;
-  __shared__ double red[4 * G];
-  double mu[P];
+__device__ __forceinline__ void factor_cov(int days, const double* __restrict__ Fr, double* __restrict__ Sf, double* fs,
+                                           double* mu) {
+  constexpr int G = RmDim<P>::G, NE = (G + RM_W - 1) / RM_W;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int ea[NE], eb[NE];
+  double s[NE];
 #pragma unroll
-  for (int a = 0; a < P; ++a) mu[a] = 0.0;
-  for (int k = threadIdx.x; k < days; k += 256)
-#pragma unroll
-    for (int a = 0; a < P; ++a) mu[a] += Fr[(size_t)k * P + a];
-  block_sum<P>(mu, red);
-#pragma unroll
-  for (int a = 0; a < P; ++a) mu[a] /= (double)days;
-  double c[G];
-#pragma unroll
-  for (int g = 0; g < G; ++g) c[g] = 0.0;
-  for (int k = threadIdx.x; k < days; k += 256) {
-    double f[P];
-#pragma unroll
-    for (int a = 0; a < P; ++a) f[a] = Fr[(size_t)k * P + a] - mu[a];
-    int g = 0;
-#pragma unroll
-    for (int a = 0; a < P; ++a)
-#pragma unroll
-      for (int b = a; b < P; ++b) { c[g] = fma(f[a], f[b], c[g]); ++g; }
+  for (int e = 0; e < NE; ++e) {   // entry (ea, eb) of the upper triangle, row-major
+    int a = 0, r = min(wave + e * RM_W, G - 1);
+    while (r >= P - a) { r -= P - a; ++a; }
+    ea[e] = a;
+    eb[e] = a + r;
   }
-  block_sum<G>(c, red);
-  if (threadIdx.x == 0) {
-    int g = 0;
-    for (int a = 0; a < P; ++a)
-      for (int b = a; b < P; ++b) {
-        const double v = c[g++] / (double)(days - 1);
-        Sf[a * P + b] = v;
-        Sf[b * P + a] = v;
+  for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) s[e] = 0.0;
+    for (int k0 = 0; k0 < days; k0 += RM_CHUNK) {
+      const int nk = min(RM_CHUNK, days - k0);
+      __syncthreads();
+      for (int e = tid; e < nk * P; e += RM_NT) fs[e] = Fr[(size_t)k0 * P + e];
+      __syncthreads();
+      for (int k = lane; k < nk; k += 64) {
+        if (pass == 0) {   // (at least as many entries as means)
+#pragma unroll
+          for (int e = 0; e < NE; ++e) s[e] += fs[k * P + min(wave + e * RM_W, P - 1)];
+        } else {
+#pragma unroll
+          for (int e = 0; e < NE; ++e) s[e] = fma(fs[k * P + ea[e]] - mu[ea[e]], fs[k * P + eb[e]] - mu[eb[e]], s[e]);
+        }
       }
+    }
+    if (pass == 0) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const double t = wave_sum(s[e]);
+        if (lane == 0 && wave + e * RM_W < P) mu[wave + e * RM_W] = t / (double)days;
+      }
+      __syncthreads();
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const double v = wave_sum(s[e]) / (double)(days - 1);
+    if (lane == 0 && wave + e * RM_W < G) {
+      Sf[ea[e] * P + eb[e]] = v;
+      Sf[eb[e] * P + ea[e]] = v;
+    }
   }
 }
 
+template <int P, bool MASKED>
+__global__ __launch_bounds__(RM_NT) __attribute__((amdgpu_waves_per_eu(2))) void k_risk(
+    int days, int n, int tiles, const double* __restrict__ R, const double* __restrict__ Fr,
+    const uint8_t* __restrict__ mask, int min_obs, double* __restrict__ beta, double* __restrict__ Sf,
+    double* __restrict__ D, int32_t* __restrict__ valid) {
+  constexpr int NV = RmDim<P>::NV, G = RmDim<P>::G;
+  __shared__ RmLds<P> L;
+  __shared__ double mu[P];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0) {   // (first, so that it is not the last one to start)
+    factor_cov<P>(days, Fr, Sf, L.fs, mu);
+    return;
+  }
+  // neighbouring tiles on one XCD: a line of the mask holds eight tiles' days
+  const int per = (tiles + RM_XCDS - 1) / RM_XCDS, bx = blockIdx.x - 1;
+  const int tile = (bx % RM_XCDS) * per + bx / RM_XCDS;
+  if (tile >= tiles) return;
+  const int a = tid & (RM_TILE - 1), grp = tid / RM_TILE, i = tile * RM_TILE + a;
+  const bool col = i < n;
+  double acc[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+  const double* Rc = R + min(i, n - 1);
+  const uint8_t* Mc = mask + (MASKED ? min(i, n - 1) : 0);
+  // every load unconditional (the last day and asset again past the end): a compare in
+  // between would wait for the load before the next one is issued
+  double rv[RM_U], rn[RM_U];
+  uint8_t mv[RM_U], mn[RM_U];
+  const auto load = [&](double (&r)[RM_U], uint8_t (&m)[RM_U], int k) {
+#pragma unroll
+    for (int u = 0; u < RM_U; ++u) {
+      const size_t at = (size_t)min(k + u * RM_GROUPS, days - 1) * n;
+      r[u] = Rc[at];
+      m[u] = MASKED ? Mc[at] : (uint8_t)1;
+    }
+  };
+  load(rv, mv, grp);
+  for (int k0 = 0; k0 < days; k0 += RM_U * RM_GROUPS) {
+    if (k0 % RM_CHUNK == 0) {
+      __syncthreads();
+      for (int e = tid; e < min(RM_CHUNK, days - k0) * P; e += RM_NT) L.fs[e] = Fr[(size_t)k0 * P + e];
+      __syncthreads();
+    }
+    load(rn, mn, k0 + RM_U * RM_GROUPS + grp);
+#pragma unroll
+    for (int u = 0; u < RM_U; ++u) {
+      const int k = k0 + u * RM_GROUPS + grp;
+      const bool ob = col && k < days && mv[u] != 0;
+      const double* fs = L.fs + min(k, days - 1) % RM_CHUNK * P;
+      double f[P];   // zero on a day that does not count, so that its terms are zero
+#pragma unroll
+      for (int b = 0; b < P; ++b) f[b] = fs[b];
+#pragma unroll
+      for (int b = 0; b < P; ++b) f[b] = ob ? f[b] : 0.0;
+      const double r = ob ? rv[u] : 0.0;
+      int g = 0;
+#pragma unroll
+      for (int b = 0; b < P; ++b)
+#pragma unroll
+        for (int c = b; c < P; ++c) { acc[g] = fma(f[b], f[c], acc[g]); ++g; }
+#pragma unroll
+      for (int b = 0; b < P; ++b) acc[G + b] = fma(f[b], r, acc[G + b]);
+      acc[G + P] += r;
+      acc[G + P + 1] = fma(r, r, acc[G + P + 1]);
+      acc[G + P + 2] += ob ? 1.0 : 0.0;
+#pragma unroll
+      for (int b = 0; b < P; ++b) acc[G + P + 3 + b] += f[b];
+    }
+#pragma unroll
+    for (int u = 0; u < RM_U; ++u) { rv[u] = rn[u]; mv[u] = mn[u]; }
+  }
+  // an asset's sums: its four lanes of a wave, then the waves in order
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < NV; v += 4) {
+    const double t0 = pair_sum32(acc[v], v + 1 < NV ? acc[v + 1] : 0.0);
+    const double t1 = v + 2 < NV ? pair_sum32(acc[v + 2], v + 3 < NV ? acc[v + 3] : 0.0) : 0.0;
+    const double t = pair_sum16(t0, t1);
+    const int ag = lane >> 4, vv = v + 2 * (ag & 1) + (ag >> 1);
+    if (vv < NV) L.red[(wave * NV + vv) * RM_TILE + a] = t;
+  }
+  __syncthreads();
+  for (int e = tid; e < NV * RM_TILE; e += RM_NT) {
+    double t = L.red[e];
+#pragma unroll
+    for (int w = 1; w < RM_W; ++w) t += L.red[w * NV * RM_TILE + e];
+    L.red[RM_W * NV * RM_TILE + e] = t;
+  }
+  __syncthreads();
+  if (tid < RM_TILE && col) solve_asset<P>(L.red + RM_W * NV * RM_TILE + tid, min_obs, i, beta, D, valid);
+}
+
 template <int P>
-int launch_rm(int days, int n, const double* R, const double* Fr, const uint8_t* mask, int min_obs, double* part,
-              double* beta, double* Sf, double* D, int32_t* valid, hipStream_t st) {
-  const int nchunk = (days + RM_CHUNK - 1) / RM_CHUNK;
-  hipLaunchKernelGGL(k_rm_cov<P>, dim3(1), dim3(256), 0, st, days, Fr, Sf);
-  hipLaunchKernelGGL(k_rm_partial<P>, dim3((n + 63) / 64, nchunk), dim3(256), 0, st, days, n, R, Fr, mask, part);
-  hipLaunchKernelGGL(k_rm_solve<P>, dim3((n + 255) / 256), dim3(256), 0, st, n, nchunk, min_obs, part, beta, D, valid);
+int launch_rm(int days, int n, const double* R, const double* Fr, const uint8_t* mask, int min_obs, double* beta,
+              double* Sf, double* D, int32_t* valid, hipStream_t st) {
+  const int tiles = (n + RM_TILE - 1) / RM_TILE, grid = 1 + (tiles + RM_XCDS - 1) / RM_XCDS * RM_XCDS;
+  if (mask)
+    hipLaunchKernelGGL((k_risk<P, true>), dim3(grid), dim3(RM_NT), 0, st, days, n, tiles, R, Fr, mask, min_obs, beta, Sf, D, valid);
+  else
+    hipLaunchKernelGGL((k_risk<P, false>), dim3(grid), dim3(RM_NT), 0, st, days, n, tiles, R, Fr, mask, min_obs, beta, Sf, D, valid);
   return (int)hipGetLastError();
 }
 
 }  // namespace
 
-size_t rm_workspace_bytes(int64_t days, int64_t n, int64_t p) {
-  const int64_t nv = p * (p + 1) / 2 + 2 * p + 3;
-  return (size_t)((days + RM_CHUNK - 1) / RM_CHUNK) * nv * n * sizeof(double);
-}
-
 int launch_risk_model(int days, int n, int p, const double* R, const double* Fr, const uint8_t* mask, int min_obs,
-                      double* part, double* beta, double* Sf, double* D, int32_t* valid, void* stream) {
+                      double* beta, double* Sf, double* D, int32_t* valid, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   switch (p) {
-    case 1: return launch_rm<1>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 2: return launch_rm<2>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 3: return launch_rm<3>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 4: return launch_rm<4>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 5: return launch_rm<5>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 6: return launch_rm<6>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 7: return launch_rm<7>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
-    case 8: return launch_rm<8>(days, n, R, Fr, mask, min_obs, part, beta, Sf, D, valid, st);
+    case 1: return launch_rm<1>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 2: return launch_rm<2>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 3: return launch_rm<3>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 4: return launch_rm<4>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 5: return launch_rm<5>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 6: return launch_rm<6>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 7: return launch_rm<7>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
+    case 8: return launch_rm<8>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
     default: return (int)hipErrorInvalidValue;
   }
 }
