@@ -433,6 +433,21 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   ffo::MpPlan mp{};
   const bool mpk = T > 0 && c.prec == ffo::PREC_FP64 && !opt.deterministic && opt.workgroups == 0 && opt.speculative <= 0 &&
                    opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::mp_plan(n, nr, (int)P, cus, lds_cap, &mp);
+  // Single-period slices whose rows do not fit in LDS read them once per iteration, in tiles
+  // (a second copy of the rows: not beyond 8 GiB of it, nor in the fixed scratch of the
+  // allocation-free entry).  FP32, 140 rows, per iteration: rows in LDS 33 us at n = 50,000 and
+  // 39 at 60,000; tiles 41 at 70,000 and 47 at 100,000, where rows read twice took 96.
+  size_t tile_bytes = 0;
+  if (!reg && !mpk && !fx && T == 0 && c.spec && !c.lds_k) {
+    ffo::DevControl t = c;
+    t.stream = ffo::stream_rows(nr);
+    t.stream_rc = c.prec == ffo::PREC_FP32 && c.lds_state;
+    t.lds_state = 0;
+    tile_bytes = ffo::stream_bytes(t.stream, nwg, nw, c.prec);
+    const size_t need = ffo::solve_lds_bytes(p, t);
+    if (t.stream && need <= lds_cap && tile_bytes <= (size_t)8 << 30) { c = t; lds = need; }
+    else tile_bytes = 0;
+  }
   // ---- workspace layout (one for both kernels) ----
   const size_t Pn = (size_t)P * n, Tpn = (size_t)Tp * n;
   size_t off = 0;
@@ -440,6 +455,7 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   const size_t oK = carve((size_t)std::max(nr, 1) * ldk, 8), odr = carve(std::max(nr, 1), 8), odc = carve(n, 8);
   const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k;   // FP32 form reading rows from device memory
   const size_t oKf = carve(f32rows ? (size_t)std::max(nr, 1) * ldk : 1, 4);
+  const size_t oKt = carve(tile_bytes, 1);
   const size_t odrC = carve(Tpn, 8), oar = carve(n, 8), ocv = carve(n, 8), oca = carve(Tpn, 8), ocb = carve(Tpn, 8);
   const size_t obF = carve(std::max<int64_t>(k, 1), 8), ocr = carve(1, 8), oC = carve(std::max<int64_t>(k * k, 1), 8);
   size_t ost[6];
@@ -516,6 +532,10 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
     if (ffo::launch_to_float(D(oK), (float*)(B + oKf), (int64_t)nr * ldk, stream))
       return fail(FFO_EDEVICE, "setup kernel launch failed");
     p.Kf = (const float*)(B + oKf);
+  }
+  if (tile_bytes) {
+    if (ffo::launch_blocks(p, c, B + oKt, stream)) return fail(FFO_EDEVICE, "setup kernel launch failed");
+    p.Kt = B + oKt;
   }
 
   ffo::DevState sv{};

@@ -30,6 +30,7 @@ struct DevProblem {
   int32_t kscaled;      // 1: K holds diag(dr) K diag(dc); 0: K holds K diag(dc), rows scaled by dr on use
   const double* K;      // [nr][ldk] constraint rows (see kscaled)
   const float* Kf;      // the same rows rounded to float (FP32 form reading rows from device memory), or null
+  const void* Kt;       // the same rows in tiles, double or float, for the one-pass form (launch_blocks), or null
   const uint16_t* Kb;   // the same rows as bfloat16 bit patterns (PREC_BF16K), or null
   const double* dr;     // [nr]
   const double* dc;     // [n]
@@ -83,6 +84,8 @@ struct DevControl {
   int32_t infeas;       // 1: test the exposure-dual displacement for an infeasibility certificate
   double omega0;        // starting primal weight (> 0)
   int32_t xgroups;      // atomic exchange: copies of the slot (workgroup w adds into copy w % xgroups)
+  int32_t stream;       // > 0: the one-pass form with rows in tiles of 16 stream rows (solve_kernel.hip)
+  int32_t stream_rc;    // that form: alpha, arisk, ca and cb rounded to float (the FP32 form's LDS copies)
   int64_t stop_at;      // row-register kernel: > 0 stops after that many iterations (a multiple of
                         // check_every) and writes the iterate itself, not T(z), to w_out and y_out
 };
@@ -140,6 +143,11 @@ int launch_solve_batch(const DevProblem* dp, const DevState* ds, const DevContro
 // Resident workgroups per CU of the batched kernel at the given dynamic LDS size.
 int solve_batch_occupancy(int kl, int sl, int prec, size_t lds_bytes);
 int solve_vmax(const DevProblem& p);
+// The one-pass form for long single-period slices: its row groups of 16 (0: too many rows),
+// the bytes of its tiles for nwg workgroups of nw assets, and their layout from K.
+int stream_rows(int nr);
+size_t stream_bytes(int ra, int nwg, int nw, int prec);
+int launch_blocks(const DevProblem& p, const DevControl& c, void* Kt, void* stream);
 
 // Single-period FP64 solve with the constraint rows in registers (reg_kernel.hip): rows in
 // ra groups of 16, 32 ca assets per workgroup, nwg workgroups.  reg_plan returns false where

@@ -1154,6 +1154,258 @@ extern __shared__ double g_lds[];
 template <class R>
 __host__ __device__ constexpr size_t lds_doubles(size_t count) { return (count * sizeof(R) + 7) / 8; }
 
+// ---------------------------------------------------------------------------------
+// One pass over rows that stream from device memory
+// ---------------------------------------------------------------------------------
+// Long slices of one period: K~^T y, the prox inputs and the affine pieces of K~ xbar from
+// one reading of the rows.  launch_blocks lays them out for it: tiles of 16 RA rows and
+// 4 CA assets, in a tile the 16 bytes of each lane for the row rg + 16 q (q < RA) and the
+// assets ag CA + c (c < CA), lane = 16 ag + rg, so that every load of a wave is 1 KB in a
+// row.  A wave takes every NWAVE-th tile of its workgroup with the next two tiles' loads in
+// flight, and keeps its row sums in registers for the whole slice; K~^T y leaves asset
+// ag CA + rg % CA in lane (ag, rg), as in reg_kernel.hip.
+//
+// What bounds it: the stream of the rows.  n = 400,000, 140 rows: FP32 50 us for 224 MB of rows
+// and 26 MB of state (5.0 TB/s), FP64 84 us for 448 + 26 MB (5.6 TB/s); the two passes over
+// the rows that it replaces took 129 and 196 us.  The iteration, with the exchange, the
+// multiplier and the other half of the assets' work: FP32 186 -> 92 us, FP64 279 -> 141; at
+// n = 100,000 FP32 96 -> 47.  Two tiles in flight against one, half the size: 53 -> 50 us.
+struct StreamArgs {
+  const void* K;                             // this workgroup's tiles
+  const double *x0, *y0, *dc, *al, *ar;      // its assets: anchors, column scale, alpha, 2 g1 delta^2
+  const void *xs, *ys;                       // and iterates
+  double* list;                              // breakpoint list of this iteration (null: none)
+  double itau, cen, hw, c2, c4, c5;          // 1 / tau; the bracket and its candidates 2, 4 and 5
+  int nwa, tiles, first, rc;                 // assets, tiles, first asset; rc: alpha and arisk rounded to float
+};
+typedef __attribute__((address_space(3))) StreamArgs lstream;
+template <class KG>
+constexpr int stream_ca() { return 16 / (int)sizeof(KG); }
+
+template <class T>
+__device__ __forceinline__ const gmem_t<T>* uniform_ptr(const T* q) {
+  const unsigned long long u = (unsigned long long)q;
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+  return (const gmem_t<T>*)(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double uniform(double x) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  return u2d((unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u),
+             (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32)));
+}
+
+// What a pass does.  ITERATE: K~^T y, then b, |b| and 1/a of the assets to bs, ab, ia, the
+// bracket statistics and each wave's sums for K~ (2 xhat(c_4) - x) and K~ d xhat / d mu in
+// part[wave][2][16 RA + SW]; ROWS: each wave's sums for K~ bs in part[wave][0]; COLS: K~^T y to bs.
+// y: LDS [16 RA], times the row scales and zero beyond the rows; lcnt counts listed breakpoints.
+enum StreamMode { ST_ITERATE, ST_ROWS, ST_COLS };
+constexpr int SW = (STW + 1) / 2;   // half the room of a wave's statistics, behind its row sums
+
+template <class KG, int RA, StreamMode MODE>
+__device__ __noinline__ void stream_pass(const lstream* A, const ldbl* y, ldbl* bs, ldbl* ab, ldbl* ia, lint* lcnt,
+                                         ldbl* part) {
+  constexpr int CA = stream_ca<KG>(), WA = 4 * CA, NRP = 16 * RA;
+  constexpr bool IT = MODE == ST_ITERATE;
+  constexpr int CQ = NC * CA / 16;   // bracket candidates of a lane: the 16 / CA lanes of an asset share them
+  typedef KG vec __attribute__((ext_vector_type(CA)));
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int rg = lane & 15, ag = lane >> 4, slot = ag * CA + (rg & (CA - 1));
+  const gmem_t<vec>* K = (const gmem_t<vec>*)uniform_ptr((const KG*)A->K);
+  const gmem_t<double>*x0 = uniform_ptr(A->x0), *y0 = uniform_ptr(A->y0), *dc = uniform_ptr(A->dc);
+  const gmem_t<double>*al = uniform_ptr(A->al), *ar = uniform_ptr(A->ar);
+  const gmem_t<KG>*xs = uniform_ptr((const KG*)A->xs), *ys = uniform_ptr((const KG*)A->ys);
+  const double itau = uniform(A->itau), c2 = uniform(A->c2), c4 = uniform(A->c4), c5 = uniform(A->c5);
+  const int nwa = __builtin_amdgcn_readfirstlane(A->nwa), tiles = __builtin_amdgcn_readfirstlane(A->tiles);
+  const int rc = __builtin_amdgcn_readfirstlane(A->rc);
+  double a1[RA], a2[RA], cq[CQ], S[CQ], A0[CQ], S0 = 0.0, mx = 0.0;
+  int N[CQ];
+#pragma unroll
+  for (int q = 0; q < RA; ++q) a1[q] = a2[q] = 0.0;
+#pragma unroll
+  for (int q = 0; q < CQ; ++q) {
+    cq[q] = IT ? cand(uniform(A->cen), uniform(A->hw), rg / CA * CQ + q) : 0.0;
+    S[q] = A0[q] = 0.0;
+    N[q] = 0;
+  }
+  struct Tile {
+    vec k[RA];
+    double x0, y0, dc, al, ar;
+    KG xs, ys;
+  };
+  // (past the end the last tile again: a load under a condition would be waited for with all
+  // that follow it)
+  const auto load = [&](Tile& t, int at) {
+    const int tile = min(at, tiles - 1);
+    if constexpr (IT) {
+      const int li = min(tile * WA + slot, nwa - 1);
+      t.xs = xs[li];
+      t.ys = ys[li];
+      if constexpr (sizeof(KG) == 4) { t.x0 = x0[li]; t.y0 = y0[li]; }
+      t.dc = dc[li];
+      t.al = al[li];
+      t.ar = ar[li];
+    }
+    const gmem_t<vec>* kt = K + (size_t)tile * (RA * 64) + lane;
+#pragma unroll
+    for (int q = 0; q < RA; ++q) t.k[q] = __builtin_nontemporal_load(kt + q * 64);
+  };
+  const auto work = [&](Tile& t, int tile) {
+    const int li = tile * WA + slot;
+    const bool val = li < nwa;
+    double x1, x2 = 0.0;
+    if constexpr (MODE == ST_ROWS) {
+      x1 = val ? (double)bs[li] : 0.0;
+    } else {
+      double v[CA];
+#pragma unroll
+      for (int e = 0; e < CA; ++e) v[e] = 0.0;
+#pragma unroll
+      for (int q = 0; q < RA; ++q) {
+        const double yq = y[rg + 16 * q];
+#pragma unroll
+        for (int e = 0; e < CA; ++e) v[e] = fma((double)t.k[q][e], yq, v[e]);
+      }
+      const auto halve = [&](auto ctrl, auto h, int bit) {
+        constexpr int H = decltype(h)::value;
+        const bool up = (rg & bit) != 0;
+#pragma unroll
+        for (int e = 0; e < H; ++e) {
+          const double keep = up ? v[e + H] : v[e], send = up ? v[e] : v[e + H];
+          v[e] = keep + dpp<decltype(ctrl)::value>(send);
+        }
+      };
+      using std::integral_constant;
+      if constexpr (CA == 4) halve(integral_constant<int, DPP_SWAP2>{}, integral_constant<int, 2>{}, 2);
+      halve(integral_constant<int, DPP_SWAP1>{}, integral_constant<int, 1>{}, 1);
+      double Ry = v[0];
+      if constexpr (CA == 2) Ry += dpp<DPP_SWAP2>(Ry);
+      Ry += dpp<DPP_ROR4>(Ry);
+      Ry += dpp<DPP_ROR8>(Ry);
+      if constexpr (MODE == ST_COLS) {
+        if (val && rg < CA) bs[li] = Ry;
+        return;
+      }
+      // the asset's prox input b = x / (tau dc) - R / dc + alpha and 1/a
+      double x, yc;
+      if constexpr (sizeof(KG) == 4) { x = t.x0 + (double)t.xs; yc = t.y0 + (double)t.ys; }
+      else { x = t.xs; yc = t.ys; }
+      const double alv = rc ? (double)(float)t.al : t.al, arv = rc ? (double)(float)t.ar : t.ar;
+      const double idc = 1.0 / t.dc, itd = idc * itau, iav = 1.0 / fma(itd, idc, arv);
+      const double b = x * itd - fma(t.dc, yc, Ry) * idc + alv, abv = val ? fabs(b) : 0.0;
+      S0 = fma(abv, iav, S0);
+      mx = fmax(mx, abv);
+#pragma unroll
+      for (int q = 0; q < CQ; ++q) {
+        const bool in = abv > cq[q];
+        S[q] += in ? (abv - cq[q]) * iav : 0.0;
+        A0[q] += in ? iav : 0.0;
+        N[q] += in;
+      }
+      if (val && rg < CA) {
+        bs[li] = b;
+        ab[li] = abv;
+        ia[li] = iav;
+        double* list = A->list;
+        if (list && abv > c2 && abv <= c5) {
+          const int pos = __hip_atomic_fetch_add(lcnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (pos < LIST_CAP) {
+            double* e = list + 1 + 4 * pos;
+            std_(e, abv);
+            std_(e + 1, iav);
+            std_(e + 2, (double)(A->first + li));
+            std_(e + 3, sgn(b) * iav * idc);
+          }
+        }
+      }
+      const double g = copysign(iav * idc, b);
+      x1 = val ? 2.0 * (abv > c4 ? g * (abv - c4) : 0.0) - x : 0.0;
+      x2 = abv > c4 ? -g : 0.0;
+      // (the rows' second use, widened again: the doubles of both uses would take twice the registers)
+      if constexpr (sizeof(KG) == 4) {
+#pragma unroll
+        for (int q = 0; q < RA; ++q)
+#pragma unroll
+          for (int e = 0; e < CA; ++e) asm volatile("" : "+v"(t.k[q][e]));
+      }
+    }
+    static_for<CA>([&](auto e) {
+      constexpr int E = decltype(e)::value;
+      const double v1 = dpp<DPP_BCAST + E>(x1), v2 = IT ? dpp<DPP_BCAST + E>(x2) : 0.0;
+#pragma unroll
+      for (int q = 0; q < RA; ++q) {
+        const double kv = (double)t.k[q][E];
+        a1[q] = fma(kv, v1, a1[q]);
+        if constexpr (IT) a2[q] = fma(kv, v2, a2[q]);
+      }
+    });
+  };
+  if (tiles > 0) {
+    Tile ta, tb, tc;
+    load(ta, wave);
+    load(tb, wave + NWAVE);
+    for (int t = wave; t < tiles; t += 3 * NWAVE) {
+      load(tc, t + 2 * NWAVE);
+      __builtin_amdgcn_sched_barrier(0);
+      work(ta, t);
+      __builtin_amdgcn_sched_barrier(0);
+      load(ta, t + 3 * NWAVE);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t + NWAVE < tiles) work(tb, t + NWAVE);
+      __builtin_amdgcn_sched_barrier(0);
+      load(tb, t + 4 * NWAVE);
+      __builtin_amdgcn_sched_barrier(0);
+      if (t + 2 * NWAVE < tiles) work(tc, t + 2 * NWAVE);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  if constexpr (MODE == ST_COLS) return;
+  ldbl* out = part + wave * 2 * (NRP + SW);
+#pragma unroll
+  for (int q = 0; q < RA; ++q) a1[q] = pair_sum32(a1[q], a2[q]);   // low half-wave: x1, high: x2
+#pragma unroll
+  for (int q = 0; q < RA; q += 2) {
+    const double s = pair_sum16(a1[q], q + 1 < RA ? a1[q + 1] : 0.0);
+    const int qq = q + (ag & 1);
+    if (qq < RA) out[(ag >> 1) * NRP + rg + 16 * qq] = s;
+  }
+  if constexpr (IT) {
+    // an asset's lanes hold the same |b| and 1/a: the sums run over the lanes of one candidate group
+    const auto over = [&](double v) {
+      v = CA == 4 ? sum4(v) : v + dpp<DPP_SWAP1>(v);
+      v = pair_sum32(v, v);
+      return pair_sum16(v, v);
+    };
+    S0 = over(S0);
+    mx = wave_max(mx);
+    ldbl* st = out + 2 * NRP;
+    if (lane == 0) { st[0] = S0; st[1] = mx; }
+#pragma unroll
+    for (int q = 0; q < CQ; ++q) {
+      const double s = over(S[q]), a = over(A0[q]), m = over((double)N[q]);
+      const int c = rg / CA * CQ + q;
+      if (ag == 0 && rg % CA == 0) { st[2 + 3 * c] = s; st[3 + 3 * c] = a; st[4 + 3 * c] = m; }
+    }
+  }
+}
+
+template <class KG, StreamMode MODE>
+__device__ __forceinline__ void stream_call(int ra, const lstream* A, const ldbl* y, ldbl* bs, ldbl* ab, ldbl* ia,
+                                            lint* lcnt, ldbl* part) {
+  switch (ra) {
+    case 1: stream_pass<KG, 1, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+    case 2: stream_pass<KG, 2, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+    case 3: stream_pass<KG, 3, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+    case 5: stream_pass<KG, 5, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+    case 7: stream_pass<KG, 7, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+    case 9: stream_pass<KG, 9, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+    case 10: stream_pass<KG, 10, MODE>(A, y, bs, ab, ia, lcnt, part); break;
+  }
+}
+__host__ __device__ inline size_t stream_lds(int ra) {
+  return (size_t)16 * ra + 2 * NWAVE * (16 * ra + SW) + (sizeof(StreamArgs) + 7) / 8;
+}
+
 // One solve by a team of nwg workgroups; this workgroup is rank wg of the team.
 // Elementwise pass over e in [0, ne) with two elements per thread and step, for per-asset
 // state in device memory: both elements' loads are issued before the first store.  With
@@ -1240,6 +1492,15 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
     pool = ptr; ptr += NPOOL * 4;
     psrc = (lint*)ptr; ptr += NPOOL / 2;
     pper = (lint*)ptr; ptr += NPOOL / 2;
+  }
+  // rows in tiles for the one-pass form (stream_pass; single-team launches only)
+  const int ra = LS && !KL && !SL ? ctl.stream : 0;
+  ldbl *ysk = nullptr, *spart = nullptr;
+  lstream* sarg = nullptr;
+  if (ra) {
+    ysk = ptr; ptr += 16 * ra;
+    spart = ptr; ptr += 2 * NWAVE * (16 * ra + SW);
+    sarg = (lstream*)ptr; ptr += (sizeof(StreamArgs) + 7) / 8;
   }
   using SV = S<KL, SL, R, KGT>;
   SV V;
@@ -1381,6 +1642,17 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
     const double y = s.y_init ? s.y_init[(size_t)P * nr + ix] / p.drC[ix] : 0.0;
     V.ys0C(t, li) = y; V.ysC.set(t, li, y); V.TysC.set(t, li, y);
   }
+  if constexpr (LS && !KL && !SL) {
+    if (ra && c.tid == 0) {
+      constexpr int WA = 4 * stream_ca<R>();
+      const int tpw = (nw + WA - 1) / WA;
+      sarg->K = (const char*)p.Kt + (size_t)c.wg * tpw * ra * 1024;
+      sarg->x0 = V.x0s.b + c.i0; sarg->y0 = V.ys0C.b + c.i0;
+      sarg->xs = V.xs.d.b + c.i0; sarg->ys = V.ysC.d.b + c.i0;
+      sarg->dc = p.dc + c.i0; sarg->al = p.alpha + c.i0; sarg->ar = p.arisk + c.i0;
+      sarg->nwa = c.nwa; sarg->tiles = (c.nwa + WA - 1) / WA; sarg->first = c.i0; sarg->rc = ctl.stream_rc;
+    }
+  }
   __syncthreads();
   const long long t_start = wall_clock64();
   long long t_check = 0;
@@ -1406,7 +1678,18 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
     wg_sum<2>(c, loc);
     if (c.tid == 0) { put(c, 0, red[RED_OUT]); put(c, 1, red[RED_OUT + 1]); }
     __syncthreads();
-    rows_prod<1>(c, V, xv1, xv1, nw, P, nr, 2);
+    if constexpr (LS && !KL && !SL) {
+      if (ra) {
+        stream_call<R, ST_ROWS>(ra, sarg, ysk, xv1, xv3, xv4, nullptr, spart);
+        __syncthreads();
+        for (int j = c.tid; j < nr; j += TB) {
+          double v = 0.0;
+          for (int w = 0; w < NWAVE; ++w) v += spart[w * 2 * (16 * ra + SW) + j];
+          put(c, 2 + j, ks[j] * v);
+        }
+      }
+    }
+    if (!ra) rows_prod<1>(c, V, xv1, xv1, nw, P, nr, 2);
     if (!xsync_x<LS>(c, 2 + P * nr)) goto barrier_fail;
     {
       const double vv = tot[0];
@@ -1414,7 +1697,15 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
       for (int e = 0; e < P * nr; ++e) kv = fma(tot[2 + e], tot[2 + e], kv);
       lam = vv > 0.0 ? kv / vv : 0.0;
       const double scale = (lam > 0.0 && vv > 0.0) ? 1.0 / (lam * sqrt(vv)) : 1.0;
-      kty_all(c, V, tot + 2, P, nr, nw, xv2);
+      if constexpr (LS && !KL && !SL) {
+        if (ra) {
+          for (int j = c.tid; j < 16 * ra; j += TB) ysk[j] = j < nr ? ks[j] * tot[2 + j] : 0.0;
+          __syncthreads();
+          stream_call<R, ST_COLS>(ra, sarg, ysk, xv2, xv3, xv4, nullptr, spart);
+          __syncthreads();
+        }
+      }
+      if (!ra) kty_all(c, V, tot + 2, P, nr, nw, xv2);
       for (int e = c.tid; e < P * c.nwa; e += TB) {
         const int t = e / c.nwa, li = e % c.nwa;
         const double r = xv2[t * nw + li];
@@ -1442,8 +1733,21 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
 
     const long long ta0 = wall_clock64();
     // Phase A: prox inputs (signed b and 1/a) for owned (t, li).
-    kty_all<LS ? 2 : 1>(c, V, ys, P, nr, nw, xv1);
-    for (int e = c.tid; e < P * c.nwa; e += TB) {
+    if constexpr (LS && !KL && !SL) {
+      if (ra) {   // ... and the affine pieces of K~ xbar; the signed b go to xv2
+        for (int j = c.tid; j < 16 * ra; j += TB) ysk[j] = j < nr ? ks[j] * ys[j] : 0.0;
+        if (c.tid == 0) {
+          sarg->itau = 1.0 / tau;
+          sarg->cen = cen[0]; sarg->hw = hw[0];
+          sarg->c2 = cand(cen[0], hw[0], 2); sarg->c4 = cand(cen[0], hw[0], 4); sarg->c5 = cand(cen[0], hw[0], 5);
+          sarg->list = lists ? list_at(s.blist, lpar, nwg, P, c.wg, 0) : nullptr;
+        }
+        __syncthreads();
+        stream_call<R, ST_ITERATE>(ra, sarg, ysk, xv2, xv3, xv4, lcnt, spart);
+      }
+    }
+    if (!ra) kty_all<LS ? 2 : 1>(c, V, ys, P, nr, nw, xv1);
+    for (int e = c.tid; !ra && e < P * c.nwa; e += TB) {
       const int t = e / c.nwa, li = e % c.nwa;
       const double Ry = xv1[t * nw + li] + kty_trade(V, V.ysC, t, li);
       const double v = V.xs(t, li) - tau * Ry;
@@ -1481,9 +1785,26 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
     {
       const int oP1 = STW * P, oP2 = oP1 + P * nr;
       const int VE1 = ctl.spec ? oP2 + P * nr : STW * P;
-      period_stats_x<LS>(c, xv3, xv4, nw, cen, hw, 0);
+      if (!ra) period_stats_x<LS>(c, xv3, xv4, nw, cen, hw, 0);
       t_b1s += wall_clock64() - tb0;
-      if (ctl.spec) {
+      if (ra) {
+        const int ws = 2 * (16 * ra + SW);   // a wave's sums
+        for (int e = c.tid; e < 2 * nr; e += TB) {
+          const int u = e >= nr, j = e - u * nr;
+          double v = 0.0;
+          for (int w = 0; w < NWAVE; ++w) v += spart[w * ws + u * 16 * ra + j];
+          put(c, oP1 + e, ks[j] * v);   // (oP2 = oP1 + nr)
+        }
+        if (c.tid < STW) {
+          double v = spart[32 * ra + c.tid];
+          for (int w = 1; w < NWAVE; ++w) {
+            const double u = spart[w * ws + 32 * ra + c.tid];
+            v = c.tid == 1 ? fmax(v, u) : v + u;
+          }
+          if (c.tid == 1) put_max(c, 1, v);
+          else put(c, c.tid, v);
+        }
+      } else if (ctl.spec) {
         // affine pieces at hi: P1 = K~ (2 xhat_s(hi) - xs), P2 = K~ d xhat_s / d mu
         for (int e = c.tid; e < P * c.nwa; e += TB) {
           const int t = e / c.nwa, li = e % c.nwa;
@@ -1650,12 +1971,23 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
         // exact K~ xbar for every period
         for (int e = c.tid; e < P * c.nwa; e += TB) {
           const int t = e / c.nwa, li = e % c.nwa;
-          const double b = V.bb(t, li), ab = fabs(b);
-          const double xh = ab > mu[t] ? sgn(b) * (ab - mu[t]) * V.aa(t, li) / V.dc(0, li) : 0.0;
+          const double b = ra ? (double)xv2[li] : V.bb(t, li), ia = ra ? (double)xv4[li] : V.aa(t, li), ab = fabs(b);
+          const double xh = ab > mu[t] ? sgn(b) * (ab - mu[t]) * ia / V.dc(0, li) : 0.0;
           xv1[t * nw + li] = 2.0 * xh - V.xs(t, li);
         }
         __syncthreads();
-        rows_prod<1>(c, V, xv1, xv1, nw, P, nr, 0);
+        if constexpr (LS && !KL && !SL) {
+          if (ra) {
+            stream_call<R, ST_ROWS>(ra, sarg, ysk, xv1, xv3, xv4, lcnt, spart);
+            __syncthreads();
+            for (int j = c.tid; j < nr; j += TB) {
+              double v = 0.0;
+              for (int w = 0; w < NWAVE; ++w) v += spart[w * 2 * (16 * ra + SW) + j];
+              put(c, j, ks[j] * v);
+            }
+          }
+        }
+        if (!ra) rows_prod<1>(c, V, xv1, xv1, nw, P, nr, 0);
         if (!xsync_x<LS>(c, P * nr)) goto barrier_fail;
         for (int e = c.tid; e < P * nr; e += TB) Kx[e] = tot[e];
         __syncthreads();
@@ -1671,6 +2003,48 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
     // Phase C: T(z).  Primal: xhat; trades and rows: dual prox.
     // The plain kernel keeps one element per step: two per step reshuffled its registers and
     // slowed the multi-period solve (state in device memory) by ~4%.
+    // (One-pass form: trade rows unscaled, no risk centre.  T(z) from b, 1/a and mu, and at
+    // once the reflected Halpern step; a checked iteration stores T(z) for the check and
+    // leaves the step to phase D.  Four elements' loads at a time.)
+    if (ra) {
+      if constexpr (LS && !KL && !SL) {
+        constexpr int U = 4;
+        const double isig = 1.0 / sigma, m_ = mu[0], rho = ctl.rho, kk = (double)sc->kk;
+        const double a1 = (kk + 1.0) / (kk + 2.0), a0 = 1.0 / (kk + 2.0);
+        const bool rc = ctl.stream_rc != 0;
+        for (int e0 = c.tid; e0 < c.nwa; e0 += U * TB) {
+          double x0[U], x[U], y0[U], yc[U], dci[U], w0[U], ca[U], cb[U];
+  #pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int li = min(e0 + u * TB, c.nwa - 1);
+            x0[u] = V.x0s(0, li); x[u] = V.xs(0, li);
+            y0[u] = V.ys0C(0, li); yc[u] = V.ysC(0, li);
+            dci[u] = V.dc(0, li); w0[u] = V.w0(0, li); ca[u] = V.ca(0, li); cb[u] = V.cb(0, li);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+  #pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const bool in = e0 + u * TB < c.nwa;
+            const int li = in ? e0 + u * TB : c.nwa - 1;
+            const double b = xv2[li], ab = fabs(b);
+            const double xh = ab > m_ ? sgn(b) * (ab - m_) * xv4[li] / dci[u] : 0.0;
+            const double vs = yc[u] + sigma * (dci[u] * (2.0 * xh - x[u]));
+            const double cau = rc ? (double)(float)ca[u] : ca[u], cbu = rc ? (double)(float)cb[u] : cb[u];
+            const double pr = prox_cost(vs * isig - w0[u], isig, cau, cbu, p.d);
+            const double yt = vs - sigma * w0[u] - sigma * pr;
+            double tx = xh, ty = yt;
+            if constexpr (sizeof(R) == 4) {   // T(z) as stored: float offsets from the anchor
+              tx = x0[u] + (double)(float)(xh - x0[u]);
+              ty = y0[u] + (double)(float)(yt - y0[u]);
+            }
+            tx = check ? xh : a1 * ((1.0 + rho) * tx - rho * x[u]) + a0 * x0[u];
+            ty = check ? yt : a1 * ((1.0 + rho) * ty - rho * yc[u]) + a0 * y0[u];
+            if (in && check) { V.Txs.set(0, li, tx); V.TysC.set(0, li, ty); }
+            if (in && !check) { V.xs.set(0, li, tx); V.ysC.set(0, li, ty); }
+          }
+        }
+      }
+    } else
     if constexpr (SL || LS) {
       for (int e = c.tid; e < P * c.nwa; e += TB) {
         const int t = e / c.nwa, li = e % c.nwa;
@@ -2053,7 +2427,8 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
     {
       const double kk = (double)sc->kk;
       const double a1 = (kk + 1.0) / (kk + 2.0), a0 = 1.0 / (kk + 2.0), rho = ctl.rho;
-      if constexpr (SL || LS) {
+      if (ra && !check) {   // (done with T(z))
+      } else if constexpr (SL || LS) {
         for (int e = c.tid; e < P * c.nwa; e += TB) {
           const int t = e / c.nwa, li = e % c.nwa;
           V.xs.set(t, li, a1 * ((1.0 + rho) * V.Txs(t, li) - rho * V.xs(t, li)) + a0 * V.x0s(t, li));
@@ -2699,6 +3074,49 @@ int solve_vmax(const DevProblem& p) {
   return (v + 63) / 64 * 64;
 }
 
+int stream_rows(int nr) {
+  for (int r : {1, 2, 3, 5, 7, 9, 10})
+    if (16 * r >= nr) return r;
+  return 0;
+}
+
+static int stream_tiles(int nw, int prec) {
+  const int wa = 4 * (prec == PREC_FP32 ? stream_ca<float>() : stream_ca<double>());
+  return (nw + wa - 1) / wa;
+}
+
+size_t stream_bytes(int ra, int nwg, int nw, int prec) { return (size_t)nwg * stream_tiles(nw, prec) * ra * 1024; }
+
+// One 16-byte vector per thread, in the order of the tiles.
+template <class KG>
+__global__ __launch_bounds__(TB) void k_blocks(const double* __restrict__ K, int n, int nr, int ldk, int nw, int tpw,
+                                               int ra, int64_t count, KG* __restrict__ out) {
+  constexpr int CA = stream_ca<KG>();
+  for (int64_t v = blockIdx.x * (int64_t)TB + threadIdx.x; v < count; v += (int64_t)gridDim.x * TB) {
+    const int lane = (int)(v & 63);
+    const int64_t tq = v >> 6, tile = tq / ra;
+    const int q = (int)(tq - tile * ra), wg = (int)(tile / tpw), tt = (int)(tile - (int64_t)wg * tpw);
+    const int r = (lane & 15) + 16 * q, l = tt * 4 * CA + (lane >> 4) * CA;
+    const int64_t i = (int64_t)wg * nw + l;
+#pragma unroll
+    for (int e = 0; e < CA; ++e)
+      out[v * CA + e] = r < nr && l + e < nw && i + e < n ? (KG)K[(size_t)r * ldk + i + e] : (KG)0;
+  }
+}
+
+int launch_blocks(const DevProblem& p, const DevControl& c, void* Kt, void* stream) {
+  const int tpw = stream_tiles(c.nw, c.prec);
+  const int64_t count = (int64_t)c.nwg * tpw * c.stream * 64;
+  const int nb = (int)std::min<int64_t>((count + TB - 1) / TB, 1 << 16);
+  if (c.prec == PREC_FP32)
+    hipLaunchKernelGGL(k_blocks<float>, dim3(nb), dim3(TB), 0, (hipStream_t)stream, p.K, p.n, p.nr, p.ldk, c.nw, tpw,
+                       c.stream, count, (float*)Kt);
+  else
+    hipLaunchKernelGGL(k_blocks<double>, dim3(nb), dim3(TB), 0, (hipStream_t)stream, p.K, p.n, p.nr, p.ldk, c.nw, tpw,
+                       c.stream, count, (double*)Kt);
+  return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
 // LDS doubles of the per-asset state (the arrays the kernel takes when it holds the
 // state in LDS, in the same order and rounding).
 template <class R>
@@ -2716,6 +3134,7 @@ size_t solve_lds_bytes(const DevProblem& p, const DevControl& c) {
   if (c.xmode == XM_LOCAL) d += 3 * (size_t)c.vmax;
   if (c.lds_state) d += f32 ? state_lds_doubles<float>(P, Tp, nw) : state_lds_doubles<double>(P, Tp, nw);
   if (c.lists) d += NPOOL * 4 + NPOOL;   // pool, and two ints per pool entry
+  if (c.stream) d += stream_lds(c.stream);
   d += (sizeof(Scal) + 7) / 8 + 2 + 5 * P + 1;   // flags, nine per-period integer arrays and nidx[P + 1]
   return d * sizeof(double);
 }
