@@ -2546,11 +2546,16 @@ __global__ __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(2))) void k_
 // leaves the solution map unchanged), and dl/dF = dl/dG C^T follows in launch_grad_F.
 struct AScal {
   double omega, eta, tau, sigma, r0, rprev, gnorm;
-  long long it, kk, restarts, checks;
+  long long it, restarts, checks;
   int done, status, restart;
 };
 
-template <bool KL>
+// SL: the arrays that every iteration reads or writes per asset in LDS (each pass over those
+// in device memory waits a memory round trip).  An unchecked iteration takes its Halpern step
+// as it forms the image.  Per iteration, set-up included, before and after: n = 2000, T = 10, 80
+// rows 17.3 and 16.0 us (125 workgroups exchange 729 sums), n = 1500, T = 0 9.8 and 8.8; with
+// the smaller slices of adjoint_workgroups n = 1000, T = 8, 60 rows 21.3 and 11.5.
+template <bool KL, bool SL>
 __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevControl ctl, double omega_in) {
   ldbl* lds = (ldbl*)g_lds;
   const int P = p.P, nr = p.nr, n = p.n, Tp = p.Tp, nw = ctl.nw, m = p.m;
@@ -2600,12 +2605,12 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
   ldbl* hi = ptr;   ptr += P;
   ldbl* mu = ptr;   ptr += P;
   ldbl* cS = ptr;   ptr += P;
-  ldbl* stu = ptr;  ptr += P;
   __attribute__((address_space(3))) AScal* sc = (__attribute__((address_space(3))) AScal*)ptr;
   ptr += (sizeof(AScal) + 7) / 8;
   lint* iflag = (lint*)ptr; ptr += 2;
   lint* fbflag = iflag + 1;
   lint* need = (lint*)ptr;
+  ptr += (P + 1) / 2 + 1;
   c.tot = tot;
   c.red = red;
   c.flag = iflag;
@@ -2620,9 +2625,29 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
     V.wT = g(p.wT ? p.wT : p.w0);
   }
   auto G = [&](double* b) { return Arr<false, double>{b, n, c.i0}; };
-  const auto xs = G(a.xs), xbar = G(a.xbar), bb = G(a.bb), sx = G(a.sx);
-  const auto lx = G(a.lx), lx0 = G(a.lx0), Tlx = G(a.Tlx);
-  const auto ysC = G(a.ysC), lyC = G(a.lyC), lyC0 = G(a.lyC0), TlyC = G(a.TlyC), nC = G(a.nC), gsf = G(a.gsf);
+  auto H = [&](const double* b, int rows) {   // an array of the iteration
+    if constexpr (SL) {
+      Arr<true, double> r{ptr, nw, 0};
+      ptr += rows * nw;
+      return r;
+    } else {
+      return Arr<false, double>{(double*)b, n, c.i0};
+    }
+  };
+  const auto xs = G(a.xs), xbar = G(a.xbar), bb = G(a.bb), ysC = G(a.ysC), gsf = G(a.gsf);
+  const auto sx = H(a.sx, P), lx = H(a.lx, P), lx0 = H(a.lx0, P), Tlx = H(a.Tlx, P);
+  const auto lyC = H(a.lyC, Tp), lyC0 = H(a.lyC0, Tp), TlyC = H(a.TlyC, Tp), nC = H(a.nC, Tp);
+  const auto gw = H(a.grad_w, P);
+  struct { const DevProblem* p; Arr<SL, double> dc, drC; } hv{&p, H(p.dc, 1), H(p.drC, Tp)};
+  // owned elements (t, li) with li fastest, a workgroup's stride apart
+  struct Walk { int t, li; };
+  const int wt = c.nwa ? TB / c.nwa : 0, wl = c.nwa ? TB % c.nwa : 0;
+  const Walk w0 = c.nwa ? Walk{c.tid / c.nwa, c.tid % c.nwa} : Walk{Tp, 0};
+  const auto next = [&](Walk& w) {
+    w.t += wt;
+    w.li += wl;
+    if (w.li >= c.nwa) { w.li -= c.nwa; ++w.t; }
+  };
   const auto tsg = G(a.tsg), trho = G(a.trho);
   const Arr<true, double> mCv{mC, nw, 0}, nbv{xv4, nw, 0};
 
@@ -2633,6 +2658,11 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
       const int j = e / nw, li = e % nw;
       Kl[j * ldl + li] = li < c.nwa ? p.K[(size_t)j * p.ldk + c.i0 + li] * ks[j] : 0.0;
     }
+  if constexpr (SL) {
+    for (Walk w = w0; w.t < P; next(w)) gw(w.t, w.li) = a.grad_w[(size_t)w.t * n + c.i0 + w.li];
+    for (Walk w = w0; w.t < Tp; next(w)) hv.drC(w.t, w.li) = p.drC[(size_t)w.t * n + c.i0 + w.li];
+    for (int li = c.tid; li < c.nwa; li += TB) hv.dc(0, li) = p.dc[c.i0 + li];
+  }
   // the solution in scaled variables
   for (int e = c.tid; e < P * c.nwa; e += TB) {
     const int t = e / c.nwa, li = e % c.nwa;
@@ -2653,7 +2683,7 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
     ly[e] = 0.0; ly0[e] = 0.0; Tly[e] = 0.0;
   }
   if (c.tid == 0) {
-    sc->omega = omega_in; sc->it = 0; sc->kk = 0; sc->restarts = 0; sc->checks = 0;
+    sc->omega = omega_in; sc->it = 0; sc->restarts = 0; sc->checks = 0;
     sc->r0 = -1.0; sc->rprev = INFINITY; sc->done = 0; sc->status = DS_RUNNING; sc->restart = 0;
     fbflag[0] = 0;
     for (int t = 0; t < P; ++t) { cen[t] = 0.0; hw[t] = 0.0; mu[t] = 0.0; need[t] = 0; }
@@ -2837,25 +2867,28 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
     if (!refactor()) goto adj_fail;
 
     // ---- adjoint iteration
-    // one application of lambda -> J^T lambda + g; leaves nu in xv3 (per owned (t, i)), mu_y
-    // in muy / mC, K~^T mu_y in xv1.  Returns false when a bounded wait expired.
-    auto apply = [&]() -> bool {
+    // N lambda_y of the rows and trades, to muy and mC
+    auto prep = [&]() {
       for (int e = c.tid; e < P * nr; e += TB) muy[e] = nR[e] * ly[e];
-      for (int e = c.tid; e < Tp * c.nwa; e += TB) {
-        const int t = e / c.nwa, li = e % c.nwa;
-        mC[t * nw + li] = nC(t, li) * lyC(t, li);
-      }
+      for (Walk w = w0; w.t < Tp; next(w)) mC[w.t * nw + w.li] = nC(w.t, w.li) * lyC(w.t, w.li);
       __syncthreads();
+    };
+    const double rho = ctl.rho;
+    long long it = 0, kk = 0;   // iterations, and since the last restart
+    // one application of lambda -> J^T lambda + g from muy and mC; leaves nu in xv3 (per
+    // owned (t, i)).  step: the reflected Halpern step at once, with muy and mC of the new
+    // lambda; else the image in Tlx, TlyC, Tly.  Returns false when a bounded wait expired.
+    auto apply = [&](bool step) -> bool {
+      const double itau = 1.0 / tau;
+      const double a1 = (double)(kk + 1) / (double)(kk + 2), a0 = 1.0 / (double)(kk + 2);
       kty_all(c, V, muy, P, nr, nw, xv1);
-      for (int e = c.tid; e < P * c.nwa; e += TB) {
-        const int t = e / c.nwa, li = e % c.nwa;
-        const double Kt = xv1[t * nw + li] + kty_trade(V, mCv, t, li);
-        xv1[t * nw + li] = Kt;
-        const double dci = V.dc(0, li);
-        const double u = (lx(t, li) + 2.0 * sigma * Kt) / dci;
-        const double ia = fabs(sx(t, li));
-        xv2[t * nw + li] = ia * u / dci;     // (1{S}/a) u / dc
-        xv3[t * nw + li] = u;
+      for (Walk w = w0; w.t < P; next(w)) {
+        const int e = w.t * nw + w.li;
+        const double Kt = xv1[e] + kty_trade(hv, mCv, w.t, w.li), idc = 1.0 / hv.dc(0, w.li);
+        const double u = (lx(w.t, w.li) + 2.0 * sigma * Kt) * idc;
+        xv1[e] = Kt;
+        xv2[e] = fabs(sx(w.t, w.li)) * u * idc;     // (1{S}/a) u / dc
+        xv3[e] = u;
       }
       __syncthreads();
       {
@@ -2869,25 +2902,38 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
       }
       rows_prod<1>(c, V, xv2, xv2, nw, P, nr, 0);
       if (!xsync(c, P * nr + P)) return false;
-      for (int t = c.tid; t < P; t += TB) stu[t] = (mu[t] > 0.0 && cS[t] > 0.0) ? tot[P * nr + t] / cS[t] : 0.0;
-      __syncthreads();
+      const auto stu = [&](int t) { return mu[t] > 0.0 && cS[t] > 0.0 ? tot[P * nr + t] / cS[t] : 0.0; };
       for (int e = c.tid; e < P * nr; e += TB) {
-        const int t = e / nr;
-        Tly[e] = muy[e] - (tot[e] - stu[t] * Kr[e]);
+        const double ty = muy[e] - (tot[e] - stu(e / nr) * Kr[e]);
+        if (step) {
+          const double y = a1 * ((1.0 + rho) * ty - rho * ly[e]) + a0 * ly0[e];
+          ly[e] = y;
+          muy[e] = nR[e] * y;
+        } else {
+          Tly[e] = ty;
+        }
       }
-      for (int e = c.tid; e < P * c.nwa; e += TB) {
-        const int t = e / c.nwa, li = e % c.nwa;
-        const double ia = fabs(sx(t, li));
-        const double nu = ia * xv3[t * nw + li] - sx(t, li) * stu[t];
-        const double dci = V.dc(0, li);
-        xv3[t * nw + li] = nu;
-        xv4[t * nw + li] = nu / dci;
-        Tlx(t, li) = nu / (tau * dci) - sigma * xv1[t * nw + li] + dci * a.grad_w[(size_t)t * n + c.i0 + li];
+      for (Walk w = w0; w.t < P; next(w)) {
+        const int e = w.t * nw + w.li;
+        const double s = sx(w.t, w.li), nu = fabs(s) * xv3[e] - s * stu(w.t);
+        const double dci = hv.dc(0, w.li), nb = nu / dci;
+        xv3[e] = nu;
+        xv4[e] = nb;
+        const double tx = nb * itau - sigma * xv1[e] + dci * gw(w.t, w.li);
+        if (step) lx(w.t, w.li) = a1 * ((1.0 + rho) * tx - rho * lx(w.t, w.li)) + a0 * lx0(w.t, w.li);
+        else Tlx(w.t, w.li) = tx;
       }
       __syncthreads();
-      for (int e = c.tid; e < Tp * c.nwa; e += TB) {
-        const int t = e / c.nwa, li = e % c.nwa;
-        TlyC(t, li) = mC[t * nw + li] - kx_trade(V, nbv, t, li);
+      for (Walk w = w0; w.t < Tp; next(w)) {
+        const int e = w.t * nw + w.li;
+        const double ty = mC[e] - kx_trade(hv, nbv, w.t, w.li);
+        if (step) {
+          const double y = a1 * ((1.0 + rho) * ty - rho * lyC(w.t, w.li)) + a0 * lyC0(w.t, w.li);
+          lyC(w.t, w.li) = y;
+          mC[e] = nC(w.t, w.li) * y;
+        } else {
+          TlyC(w.t, w.li) = ty;
+        }
       }
       __syncthreads();
       return true;
@@ -2907,9 +2953,10 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
       if (c.tid == 0) sc->gnorm = sqrt(tot[0]);
       __syncthreads();
     }
+    prep();
     while (true) {
-      if (!apply()) goto adj_fail;
-      const bool check = ((sc->it + 1) % ctl.check_every == 0) || (sc->it + 1 >= ctl.max_iter);
+      const bool check = ((it + 1) % ctl.check_every == 0) || (it + 1 >= ctl.max_iter);
+      if (!apply(!check)) goto adj_fail;
       if (check) {
         // [residual^2, non-finite count, |T lambda_x - anchor|^2, |T lambda_y - anchor|^2]
         double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -2948,17 +2995,17 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
             a.info[IX_RELKKT] = res;
             a.info[IX_FPR] = res;
             if (ctl.verbose >= 2)
-              printf("[ffo adjoint] it %lld res %.3e omega %.3e |dlx| %.3e |dly| %.3e restarts %lld\n", sc->it + 1, res,
+              printf("[ffo adjoint] it %lld res %.3e omega %.3e |dlx| %.3e |dly| %.3e restarts %lld\n", it + 1, res,
                      sc->omega, sqrt(tot[2]), sqrt(tot[3]), sc->restarts);
           }
           if (tot[1] > 0.0 || !isfinite(res)) { sc->done = 1; sc->status = DS_NUMERIC; }
           else if (res <= ctl.tol) { sc->done = 1; sc->status = DS_OK; }
           else if (tot[4] > 0.0) { sc->done = 1; sc->status = DS_TIMEOUT; }
-          else if (sc->it + 1 >= ctl.max_iter) { sc->done = 1; sc->status = DS_NOT_CONVERGED; }
+          else if (it + 1 >= ctl.max_iter) { sc->done = 1; sc->status = DS_NOT_CONVERGED; }
           else {
             if (sc->r0 < 0.0) sc->r0 = res;
             const bool rs = (res <= ctl.r_suff * sc->r0) || (res <= ctl.r_nec * sc->r0 && res > sc->rprev) ||
-                            ((double)(sc->kk + 1) >= ctl.r_art * (double)(sc->it + 1));
+                            ((double)(kk + 1) >= ctl.r_art * (double)(it + 1));
             sc->rprev = res;
             // the weight stays fixed: unlike the solve's, this fixed point moves with
             // (tau, sigma), so a new weight would discard the progress made
@@ -2980,14 +3027,12 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
           }
           for (int e = c.tid; e < P * nr; e += TB) { ly[e] = Tly[e]; ly0[e] = Tly[e]; }
           __syncthreads();
-          if (c.tid == 0) { sc->kk = 0; sc->it++; }
-          __syncthreads();
+          prep();
+          kk = 0;
+          ++it;
           continue;
         }
-      }
-      {
-        const double kk = (double)sc->kk;
-        const double a1 = (kk + 1.0) / (kk + 2.0), a0 = 1.0 / (kk + 2.0), rho = ctl.rho;
+        const double a1 = (double)(kk + 1) / (double)(kk + 2), a0 = 1.0 / (double)(kk + 2);
         for (int e = c.tid; e < P * c.nwa; e += TB) {
           const int t = e / c.nwa, li = e % c.nwa;
           lx(t, li) = a1 * ((1.0 + rho) * Tlx(t, li) - rho * lx(t, li)) + a0 * lx0(t, li);
@@ -2998,10 +3043,12 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
         }
         for (int e = c.tid; e < P * nr; e += TB) ly[e] = a1 * ((1.0 + rho) * Tly[e] - rho * ly[e]) + a0 * ly0[e];
         __syncthreads();
-        if (c.tid == 0) { sc->kk++; sc->it++; }
-        __syncthreads();
+        prep();
       }
+      ++kk;
+      ++it;
     }
+    if (c.tid == 0) sc->it = it;
     // ---- gradients at the final lambda (one more application gives nu, mu_y)
     for (int e = c.tid; e < P * c.nwa; e += TB) {
       const int t = e / c.nwa, li = e % c.nwa;
@@ -3013,7 +3060,9 @@ __global__ __launch_bounds__(TB) void k_adjoint(DevProblem p, AdjState a, DevCon
     }
     for (int e = c.tid; e < P * nr; e += TB) ly[e] = Tly[e];
     __syncthreads();
-    if (!apply()) goto adj_fail;
+    prep();
+    // (muy keeps N lambda_y: the image goes to Tly)
+    if (!apply(false)) goto adj_fail;
     for (int e = c.tid; e < P * c.nwa; e += TB) {
       const int t = e / c.nwa, li = e % c.nwa;
       a.grad_alpha[(size_t)t * n + c.i0 + li] = xv3[t * nw + li];
@@ -3194,15 +3243,17 @@ size_t adjoint_lds_bytes(const DevProblem& p, const DevControl& c) {
   const size_t P = p.P, Tp = p.Tp, nr = p.nr, nw = c.nw;
   size_t d = 0;
   if (c.lds_k) d += nr * (nw | 1);
-  d += nr + 8 * P * nr + 4 * P * nw + Tp * nw + (size_t)c.vmax + RED_LEN + 7 * P;
+  d += nr + 8 * P * nr + 4 * P * nw + Tp * nw + (size_t)c.vmax + RED_LEN + 6 * P;
   d += (sizeof(AScal) + 7) / 8 + 2 + (P + 1) / 2 + 1;
+  if (c.lds_state) d += (5 * P + 5 * Tp + 1) * nw;
   return d * sizeof(double);
 }
 
 int launch_adjoint(const DevProblem& p, const AdjState& a, const DevControl& c, double omega, void* stream,
                    size_t lds) {
   void* args[] = {(void*)&p, (void*)&a, (void*)&c, (void*)&omega};
-  const void* fn = c.lds_k ? (const void*)k_adjoint<true> : (const void*)k_adjoint<false>;
+  const void* fn = c.lds_k ? (c.lds_state ? (const void*)k_adjoint<true, true> : (const void*)k_adjoint<true, false>)
+                           : (const void*)k_adjoint<false, false>;
   hipError_t e = hipLaunchCooperativeKernel(fn, dim3(c.nwg), dim3(TB), args, (unsigned int)lds, (hipStream_t)stream);
   return e == hipSuccess ? 0 : (int)e;
 }
