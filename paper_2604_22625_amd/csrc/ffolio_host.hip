@@ -428,13 +428,13 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
     }
     if (!placed) return fail(FFO_EINVAL, "problem too large for the per-workgroup working set (reduce m + k or T)");
   }
-  // Single-period FP64 solves keep the rows in registers where they fit (up to 160 rows and
+  // Single-period solves keep the rows in registers where they fit (up to 160 rows and
   // one workgroup per compute unit); the options that choose the exchange, the grid or the
   // per-check output of the general kernel, and impact exponents without a closed prox, stay
   // with that kernel.  Per iteration there and here: n = 77, 11 rows 15 and 2.8 us; n = 500,
   // 30 rows 12.9 and 4.3; n = 3000, 22 rows 13.8 and 6.0; n = 5000, 140 rows 14.7 and 6.9.
   ffo::RegPlan rp{};
-  const bool reg = T == 0 && c.prec == ffo::PREC_FP64 && !opt.deterministic && opt.workgroups == 0 && c.spec &&
+  const bool reg = T == 0 && !opt.deterministic && opt.workgroups == 0 && c.spec &&
                    opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::reg_plan(n, nr, cus, &rp);
   // The same for multi-period solves of up to 31 periods and 112 rows.  Per iteration there
   // and here: T = 20, n = 3000, 100 rows 67.5 and 26.5 us; T = 10, n = 2000, 80 rows 31.9 and
@@ -450,19 +450,20 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   if (!reg && !mpk && !fx && T == 0 && c.spec && !c.lds_k) {
     ffo::DevControl t = c;
     t.stream = ffo::stream_rows(nr);
-    t.stream_rc = c.prec == ffo::PREC_FP32 && c.lds_state;
+    t.rc32 = c.prec == ffo::PREC_FP32 && c.lds_state;
     t.lds_state = 0;
     tile_bytes = ffo::stream_bytes(t.stream, nwg, nw, c.prec);
     const size_t need = ffo::solve_lds_bytes(p, t);
     if (t.stream && need <= lds_cap && tile_bytes <= (size_t)8 << 30) { c = t; lds = need; }
     else tile_bytes = 0;
   }
+  if (reg) c.rc32 = c.prec == ffo::PREC_FP32 && c.lds_state;
   // ---- workspace layout (one for both kernels) ----
   const size_t Pn = (size_t)P * n, Tpn = (size_t)Tp * n;
   size_t off = 0;
   auto carve = [&](size_t cnt, size_t elt) { const size_t o = off; off = align_up(off + cnt * elt); return o; };
   const size_t oK = carve((size_t)std::max(nr, 1) * ldk, 8), odr = carve(std::max(nr, 1), 8), odc = carve(n, 8);
-  const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k;   // FP32 form reading rows from device memory
+  const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k && !reg;   // FP32 form reading rows from device memory
   const size_t oKf = carve(f32rows ? (size_t)std::max(nr, 1) * ldk : 1, 4);
   const size_t oKt = carve(tile_bytes, 1);
   const size_t odrC = carve(Tpn, 8), oar = carve(n, 8), ocv = carve(n, 8), oca = carve(Tpn, 8), ocb = carve(Tpn, 8);
@@ -1130,7 +1131,7 @@ ffo_status launch_teams(const TeamPlan& tp, int W, const std::vector<int>& ckl, 
   return FFO_OK;
 }
 
-// The teams of many single-period FP64 instances on the row-register kernel: one plan (rows
+// The teams of many single-period instances on the row-register kernel: one plan (rows
 // and assets per lane) for all, each instance's workgroups, and the ticket order (decreasing
 // size, so that the longest solves start first).
 struct RegTeams {
@@ -1140,9 +1141,9 @@ struct RegTeams {
   int grid = 0;
 };
 
-bool plan_reg_teams(int64_t B, const int64_t* n_b, int nr, int64_t T, int prec, double d, const ffo_options& opt,
+bool plan_reg_teams(int64_t B, const int64_t* n_b, int nr, int64_t T, bool prec_ok, double d, const ffo_options& opt,
                     int cus, RegTeams* out) {
-  if (T != 0 || prec != ffo::PREC_FP64 || opt.speculative == 0 || opt.verbose >= 2 || !(d == 1.5 || d == 2.0)) return false;
+  if (T != 0 || !prec_ok || opt.speculative == 0 || opt.verbose >= 2 || !(d == 1.5 || d == 2.0)) return false;
   int64_t n_max = 0;
   for (int64_t b = 0; b < B; ++b) n_max = std::max(n_max, n_b[b]);
   RegTeams& t = *out;
@@ -1599,7 +1600,8 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   // in lockstep, 206 here).  deterministic keeps the lockstep form, whose sums have a
   // fixed order.
   RegTeams rt;
-  const bool reg = opt.batched_form != 2 && !(lockstep && opt.deterministic) && plan_reg_teams(B, n_b, nr, 0, prec, d, opt, cus, &rt);
+  const bool reg = opt.batched_form != 2 && !(lockstep && opt.deterministic) && 
+                   plan_reg_teams(B, n_b, nr, 0, prec == ffo::PREC_FP64, d, opt, cus, &rt);
   const bool as_lockstep = lockstep && reg;
   if (lockstep && !reg)
     return batched_lockstep(B, n_b, n_max, k, m, F, Omega, delta, A, offs, alpha, s, q, w0, L, U, d, GMV, lambda1,
@@ -1929,11 +1931,11 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   if (occ < 1) return fail(FFO_EDEVICE, "the batched solve kernel cannot be resident");
   const int W = occ * cus;
   const TeamPlan tp = plan_teams(B, n, W, NW_MAX, NW_MIN);
-  // single-period FP64 markets on the row-register kernel (ten n = 5000 markets, 140 rows:
+  // single-period markets on the row-register kernel (FP64, ten n = 5000 markets, 140 rows:
   // 271 ms in the general team kernel, whose 25 workgroups per market read their rows from device
   // memory, 30 ms here)
   RegTeams rt;
-  const bool reg = plan_reg_teams(B, n, nr, T, prec, d, opt, cus, &rt);
+  const bool reg = plan_reg_teams(B, n, nr, T, prec == ffo::PREC_FP64 || prec == ffo::PREC_FP32, d, opt, cus, &rt);
   const std::vector<int>& g = reg ? rt.g : tp.g;
 
   // ---- workspace: each instance's scaled rows, scales, costs and state, as ffo_solve's ----
@@ -1949,7 +1951,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
     const size_t nb = (size_t)n[b];
     r.ldk = (int)((n[b] + 63) / 64 * 64);
     r.K = carve((size_t)std::max(nr, 1) * r.ldk, 8);
-    r.Kf = carve(prec == ffo::PREC_FP32 ? (size_t)std::max(nr, 1) * r.ldk : 1, 4);
+    r.Kf = carve(prec == ffo::PREC_FP32 && !reg ? (size_t)std::max(nr, 1) * r.ldk : 1, 4);
     r.dr = carve(std::max(nr, 1), 8); r.dc = carve(nb, 8); r.drC = carve(Tp * nb, 8); r.ar = carve(nb, 8);
     r.cv = carve(nb, 8); r.ca = carve(Tp * nb, 8); r.cb = carve(Tp * nb, 8);
     r.bF = carve(std::max<int64_t>(k, 1), 8); r.cr = carve(1, 8); r.C = carve(std::max<int64_t>(k * k, 1), 8);
@@ -2018,7 +2020,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
                           q[b], T ? w_target[b] : nullptr, g1, g2, g3, D(r.K), D(r.dr), D(r.dc), D(r.drC), D(r.ar),
                           D(r.cv), D(r.ca), D(r.cb), D(r.bF), D(r.cr), stream))
       return fail(FFO_EDEVICE, "setup kernel launch failed");
-    if (prec == ffo::PREC_FP32 && ffo::launch_to_float(D(r.K), (float*)(Bd + r.Kf), (int64_t)nr * r.ldk, stream))
+    if (prec == ffo::PREC_FP32 && !reg && ffo::launch_to_float(D(r.K), (float*)(Bd + r.Kf), (int64_t)nr * r.ldk, stream))
       return fail(FFO_EDEVICE, "setup kernel launch failed");
     ffo::DevProblem p = p0;
     p.n = (int)n[b]; p.ldk = r.ldk;
@@ -2052,7 +2054,18 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   // ---- LDS placement, records to the device, one cooperative launch per chunk ----
   std::vector<int> ckl, csl;
   std::vector<size_t> clds;
-  if (!reg) place_teams(tp, hP, hCt, prec, lds_lim, cus, ckl, csl, clds);
+  if (!reg) {
+    place_teams(tp, hP, hCt, prec, lds_lim, cus, ckl, csl, clds);
+  } else if (prec == ffo::PREC_FP32) {   // values rounded as where the general teams keep their state
+    std::vector<ffo::DevControl> t(B, c0);
+    for (int64_t b = 0; b < B; ++b) {
+      t[b].nwg = tp.g[b];
+      t[b].nw = (int)((n[b] + tp.g[b] - 1) / tp.g[b]);
+      t[b].xmode = tp.g[b] == 1 ? ffo::XM_LOCAL : ffo::XM_ATOMIC;
+    }
+    place_teams(tp, hP, t.data(), prec, lds_lim, cus, ckl, csl, clds);
+    for (int64_t b = 0; b < B; ++b) hCt[b].rc32 = t[b].lds_state;
+  }
   HIPCHK(hipMemcpyAsync(Bd + oP, hP, (size_t)B * sizeof(ffo::DevProblem), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));

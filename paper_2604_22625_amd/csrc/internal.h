@@ -85,7 +85,8 @@ struct DevControl {
   double omega0;        // starting primal weight (> 0)
   int32_t xgroups;      // atomic exchange: copies of the slot (workgroup w adds into copy w % xgroups)
   int32_t stream;       // > 0: the one-pass form with rows in tiles of 16 stream rows (solve_kernel.hip)
-  int32_t stream_rc;    // that form: alpha, arisk, ca and cb rounded to float (the FP32 form's LDS copies)
+  int32_t rc32;         // that form and the row-register kernel in FP32: alpha, arisk, ca and cb rounded to
+                        // float, as the FP32 form's copies in LDS are
   int64_t stop_at;      // row-register kernel: > 0 stops after that many iterations (a multiple of
                         // check_every) and writes the iterate itself, not T(z), to w_out and y_out
 };
@@ -149,7 +150,7 @@ int stream_rows(int nr);
 size_t stream_bytes(int ra, int nwg, int nw, int prec);
 int launch_blocks(const DevProblem& p, const DevControl& c, void* Kt, void* stream);
 
-// Single-period FP64 solve with the constraint rows in registers (reg_kernel.hip): rows in
+// Single-period solve with the constraint rows in registers (reg_kernel.hip): rows in
 // ra groups of 16, 32 ca assets per workgroup, nwg workgroups.  reg_plan returns false where
 // the rows or the assets do not fit (more than 160 rows, or more workgroups than cus).
 struct RegPlan {

@@ -1,4 +1,4 @@
-// Single-period solve with the constraint rows in registers (FP64, impact exponent 3/2 or 2).
+// Single-period solve with the constraint rows in registers (impact exponent 3/2 or 2).
 //
 // Same iteration as solve_kernel.hip (restarted, reflected Halpern PDHG with the exact
 // budget multiplier), laid out for one period: a team of workgroups of eight waves, two
@@ -15,6 +15,13 @@
 // Iterates and step constants stay in registers, restart anchors and asset data in LDS;
 // rows [0, 16 RA) belong to the first 16 RA threads.  Control scalars are computed by
 // every thread from the same totals, so no thread waits for a broadcast of a decision.
+//
+// In the FP32 form (ctl.prec) the values are the general kernel's: rows rounded to float,
+// iterates float offsets from the restart anchor, FP64 everywhere else, and exact rows again
+// for a check, whose block every lane reloads.  The arithmetic is the FP64 form's: half the
+// width would save none of the chains that bound an iteration.  FP32 solves on the general
+// kernel and here: n = 473, 95 rows 22.4 and 9.1 ms, n = 1777, 41 rows 39.6 and 17.1, n = 4935,
+// 70 rows 55.7 and 28.7; four markets of 419 assets, 73 rows, 52.5 and 13.3.
 //
 // What bounds it: latency.  At n = 5000, 140 rows (20 workgroups of 250 assets) an iteration
 // takes 6.9 us (14.7 in the general kernel): about 2 for the exchange between the
@@ -326,6 +333,9 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
   const int n = p.n, nr = p.nr, m = p.m, nwg = ctl.nwg;
   const int i0 = wg * ctl.nw, nwa = max(0, min(ctl.nw, n - i0));
   const double rho = ctl.rho, d = p.d, g1 = p.g1;
+  const bool f32 = ctl.prec == PREC_FP32, rc32 = f32 && ctl.rc32;
+  const auto rc = [rc32](double v) { return rc32 ? (double)(float)v : v; };
+  const auto stored = [f32](double v, double z0) { return f32 ? z0 + (double)(float)(v - z0) : v; };   // an iterate
 
   RegX X = team_init(s, ctl, wg);
 
@@ -341,7 +351,8 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
 #pragma unroll
       for (int c = 0; c < CA; ++c) {
         const int l = wave * WA + ag * CA + c;
-        K[q][c] = r < nr && l < nwa ? p.K[(size_t)r * p.ldk + i0 + l] * sc : 0.0;
+        const double k = r < nr && l < nwa ? p.K[(size_t)r * p.ldk + i0 + l] : 0.0;
+        K[q][c] = (f32 ? (double)(float)k : k) * sc;
       }
     }
     for (int e = tid; e < NWV * L.PV; e += NT) (&L.part[0][0])[e] = 0.0;
@@ -413,7 +424,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
     while (true) {
       const double sigma = uni(eta * omega), isig = uni(1.0 / sigma);
       const double idc = 1.0 / dc, itd = omega / eta * idc;          // b = x / (tau dc) - R / dc + alpha
-      const double ia = 1.0 / (itd * idc + L.ar[tid0]), gia = ia * idc;
+      const double ia = 1.0 / (itd * idc + rc(L.ar[tid0])), gia = ia * idc;
       if (tid0 < nr) {
         const double dr = L.dr[tid0], sd = sigma * dr;
         L.sd[tid0] = sd;
@@ -429,7 +440,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
         const double k1 = (double)kk, a0 = uni(recip(k1 + 2.0)), a1 = uni((k1 + 1.0) * a0);
         // prox input b and the statistics at the bracket candidates
         const double Ry = kty(K, L.y, tid) + dc * yc;
-        const double b = x * itd - Ry * idc + L.al[tid], ab = fabs(b);
+        const double b = x * itd - Ry * idc + rc(L.al[tid]), ab = fabs(b);
         if (rg < CA) { L.ab[wave][slot] = val ? ab : 0.0; L.ia[wave][slot] = val ? ia : 0.0; }
         __builtin_amdgcn_wave_barrier();
         stats<WA>(L.ab[wave], L.ia[wave], cen, hw, L.part[wave], tid);
@@ -469,11 +480,12 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
         predict(mu, mprev, wid, cen, hw);
 
         // T(z): primal point, trade duals, row duals
-        tx = ab > mu ? copysign(gia, b) * (ab - mu) : 0.0;
         {
-          const double w0 = L.w0[tid], vs = yc + sigma * (dc * (2.0 * tx - x));
-          const double pr = prox15(vs * isig - w0, isig * L.ca[tid], isig * L.cb[tid], d);
-          ty = vs - sigma * w0 - sigma * pr;
+          const double xh = ab > mu ? copysign(gia, b) * (ab - mu) : 0.0;
+          const double w0 = L.w0[tid], vs = yc + sigma * (dc * (2.0 * xh - x));
+          const double pr = prox15(vs * isig - w0, isig * rc(L.ca[tid]), isig * rc(L.cb[tid]), d);
+          tx = stored(xh, L.x0[tid]);
+          ty = stored(vs - sigma * w0 - sigma * pr, L.y0[tid]);
         }
         if (rown) {
           const double vs = fma(sigma, kx, L.y[tid]), sd = L.sd[tid], rs = L.rs[tid];
@@ -498,6 +510,18 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
           const auto [tid, lane, wave, rg, slot, li, val, mine, rown] = place<CA>(tid0, nwa, nr);
           const int i = i0 + li;
           const double al = L.al[tid], ar = L.ar[tid];
+          if (f32) {   // the check is of the unrounded problem
+            const int ag = (tid >> 4) & 3;
+#pragma unroll
+            for (int q = 0; q < RA; ++q) {
+              const int r = rg + 16 * q;
+#pragma unroll
+              for (int c = 0; c < CA; ++c) {
+                const int l = wave * WA + ag * CA + c;
+                K[q][c] = r < nr && l < nwa ? p.K[(size_t)r * p.ldk + i0 + l] : 0.0;
+              }
+            }
+          }
           // terms of the sums, one by one through LDS: fixed-point residual, |dx|^2, |dy|^2,
           // Phi's linear and quadratic part, costs, their conjugates, y_C . w0, |y|^2, time-out,
           // non-finite count, dual-domain violation^2, budget
@@ -672,6 +696,12 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
             return;
           }
         }
+        if (check && f32) {
+#pragma unroll
+          for (int q = 0; q < RA; ++q)
+#pragma unroll
+            for (int c = 0; c < CA; ++c) K[q][c] = (double)(float)K[q][c];
+        }
         // reflected Halpern step, or the restart at T(z)
         if (restart) {
           x = tx;
@@ -681,8 +711,8 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
           if (rown) L.y[tid] = L.y0r[tid] = L.ty[tid];
           kk = 0;
         } else {
-          x = a1 * ((1.0 + rho) * tx - rho * x) + a0 * L.x0[tid];
-          yc = a1 * ((1.0 + rho) * ty - rho * yc) + a0 * L.y0[tid];
+          x = stored(a1 * ((1.0 + rho) * tx - rho * x) + a0 * L.x0[tid], L.x0[tid]);
+          yc = stored(a1 * ((1.0 + rho) * ty - rho * yc) + a0 * L.y0[tid], L.y0[tid]);
           if (rown) L.y[tid] = a1 * ((1.0 + rho) * L.ty[tid] - rho * L.y[tid]) + a0 * L.y0r[tid];
           ++kk;
         }

@@ -1650,7 +1650,7 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
       sarg->x0 = V.x0s.b + c.i0; sarg->y0 = V.ys0C.b + c.i0;
       sarg->xs = V.xs.d.b + c.i0; sarg->ys = V.ysC.d.b + c.i0;
       sarg->dc = p.dc + c.i0; sarg->al = p.alpha + c.i0; sarg->ar = p.arisk + c.i0;
-      sarg->nwa = c.nwa; sarg->tiles = (c.nwa + WA - 1) / WA; sarg->first = c.i0; sarg->rc = ctl.stream_rc;
+      sarg->nwa = c.nwa; sarg->tiles = (c.nwa + WA - 1) / WA; sarg->first = c.i0; sarg->rc = ctl.rc32;
     }
   }
   __syncthreads();
@@ -2011,7 +2011,7 @@ __device__ __forceinline__ void solve_body(const DevProblem& p, const DevState& 
         constexpr int U = 4;
         const double isig = 1.0 / sigma, m_ = mu[0], rho = ctl.rho, kk = (double)sc->kk;
         const double a1 = (kk + 1.0) / (kk + 2.0), a0 = 1.0 / (kk + 2.0);
-        const bool rc = ctl.stream_rc != 0;
+        const bool rc = ctl.rc32 != 0;
         for (int e0 = c.tid; e0 < c.nwa; e0 += U * TB) {
           double x0[U], x[U], y0[U], yc[U], dci[U], w0[U], ca[U], cb[U];
   #pragma unroll
