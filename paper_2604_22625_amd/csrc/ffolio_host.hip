@@ -433,9 +433,13 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   // per-check output of the general kernel, and impact exponents without a closed prox, stay
   // with that kernel.  Per iteration there and here: n = 77, 11 rows 15 and 2.8 us; n = 500,
   // 30 rows 12.9 and 4.3; n = 3000, 22 rows 13.8 and 6.0; n = 5000, 140 rows 14.7 and 6.9.
+  // FP32 up to 64 workgroups (n = 4935, 70 rows 14.6 and 7.5): a solve that its budget of
+  // iterations cuts off shows which way single float roundings fell, 2e-8 of the weights
+  // between the two kernels at n = 59,140 and 512 iterations, 1e-8 between two runs of one.
   ffo::RegPlan rp{};
   const bool reg = T == 0 && !opt.deterministic && opt.workgroups == 0 && c.spec &&
-                   opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::reg_plan(n, nr, cus, &rp);
+                   opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::reg_plan(n, nr, cus, &rp) &&
+                   (c.prec == ffo::PREC_FP64 || rp.nwg <= 64);
   // The same for multi-period solves of up to 31 periods and 112 rows.  Per iteration there
   // and here: T = 20, n = 3000, 100 rows 67.5 and 26.5 us; T = 10, n = 2000, 80 rows 31.9 and
   // 16.5; T = 10, n = 3000, 22 rows 21.9 and 11.7; T = 5, n = 50, 8 rows 14.7 and 4.9.

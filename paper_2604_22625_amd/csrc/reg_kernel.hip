@@ -437,7 +437,11 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
         const bool check = --left == 0;
         if (check) left = (int)min((long long)ctl.check_every, ctl.max_iter - (it + 1));
         // Halpern weights of this iteration (here, off the chain that follows the exchange)
-        const double k1 = (double)kk, a0 = uni(recip(k1 + 2.0)), a1 = uni((k1 + 1.0) * a0);
+        // (FP32: the quotients themselves, since the first steps from an anchor fall on ties of the
+        // float offsets, which the last bit of a weight decides)
+        const double k1 = (double)kk;
+        double a0 = uni(recip(k1 + 2.0)), a1 = uni((k1 + 1.0) * a0);
+        if (f32) { a0 = uni(1.0 / (k1 + 2.0)); a1 = uni((k1 + 1.0) / (k1 + 2.0)); }
         // prox input b and the statistics at the bracket candidates
         const double Ry = kty(K, L.y, tid) + dc * yc;
         const double b = x * itd - Ry * idc + rc(L.al[tid]), ab = fabs(b);
