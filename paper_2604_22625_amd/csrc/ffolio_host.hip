@@ -720,6 +720,10 @@ hipError_t ls_start(const ffo::LsShared& S, const LsTune& tu, int gA, int gC, co
 // ~12 us for an iteration of the plain kernel).
 constexpr int64_t kHandoff = 4;
 
+// Checks of which the row-register teams that stand in for the lockstep form keep the iterates
+// of every instance: the longest of 256 ran 17 checks past the hand-off.
+constexpr int64_t kSnaps = 32;
+
 // Finishes instance b (n_b assets at offset o of the packed vectors) on the plain solve from
 // the iterate (w, y) after `it` iterations; rows: scratch for its m exposure rows.
 ffo_status finish_plain(int64_t b, int64_t nb, int64_t o, int64_t n_max, int64_t k, int64_t m, const double* F,
@@ -1601,7 +1605,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
                    : (opt.precision == FFO_FP32_BF16K ? ffo::PREC_BF16K : ffo::PREC_FP64);
   // The row-register teams where they apply; unless a form is asked for they also stand in
   // for the lockstep form, with its results (256 instances, n 500 to 8000, 70 rows: 385 ms
-  // in lockstep, 206 here).  deterministic keeps the lockstep form, whose sums have a
+  // in lockstep, 171 here).  deterministic keeps the lockstep form, whose sums have a
   // fixed order.
   RegTeams rt;
   const bool reg = opt.batched_form != 2 && !(lockstep && opt.deterministic) && 
@@ -1677,6 +1681,12 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const int64_t hand = as_lockstep && B > kHandoff ? kHandoff : 0;
   const size_t ohw = carve(hand ? (size_t)hand * n_max : 1, 8), ohy = carve(hand ? (size_t)hand * (nr + n_max) : 1, 8);
   const size_t ohA = carve(hand ? (size_t)std::max<int64_t>(m, 1) * n_max : 1, 8);
+  // every instance's iterates after its last kSnaps checks, unless they take over 1 GiB
+  const auto snap_doubles = [&](int64_t b) { return (size_t)(2 * n_b[b] + nr + 2); };
+  const bool snaps = hand && (2 * N + B * (nr + 2)) * kSnaps * 8 <= (int64_t)1 << 30;
+  std::vector<size_t> osn(B, 0);
+  if (snaps)
+    for (int64_t b = 0; b < B; ++b) osn[b] = carve(snap_doubles(b) * kSnaps, 8);
   const size_t total = off;
   size_t hoff = 0;
   auto hcarve = [&](size_t bytes) { const size_t o = hoff; hoff = align_up(hoff + bytes); return o; };
@@ -1764,6 +1774,11 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     if (reg) { c.xgroups = reg_xgroups(g[b]); c.vmax = ffo::reg_vmax(rt.plan.ra); }
     hCt[b] = c;
   }
+  if (snaps)
+    for (int64_t b = 0; b < B; ++b) {
+      hS[b].snaps = D(osn[b]);
+      hCt[b].snaps = kSnaps;
+    }
   std::vector<int> ckl, csl;
   std::vector<size_t> clds;
   if (!reg) place_teams(tp, hP, hCt, prec, std::min<size_t>(prop.sharedMemPerBlock, 160 * 1024), cus, ckl, csl, clds);
@@ -1798,51 +1813,74 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
 
   // ---- the lockstep form's hand-off: there, at the first check that leaves at most
   // kHandoff instances, these go on as warm-started plain solves.  That check is the
-  // iteration count of the (kHandoff + 1)-th longest solve.  The longer ones run again up to
-  // it (the same iterations, all of them side by side) and go on from there.
+  // iteration count of the (kHandoff + 1)-th longest solve.  The longer ones go on from their
+  // iterates there; those that ran more than kSnaps checks past it, or kept none, run again up
+  // to it first (the same iterations, all of them side by side).
   std::vector<int64_t> its(B);
   for (int64_t b = 0; b < B; ++b) its[b] = infos[b].iters;
   std::nth_element(its.begin(), its.begin() + kHandoff, its.end(), std::greater<int64_t>());
-  const int64_t at = its[kHandoff];
+  const int64_t at = its[kHandoff], ce = opt.check_every;
+  struct Left { int64_t b; const double *w, *y; double omega; int64_t restarts; };
+  std::vector<Left> left;
   RegTeams ht;
   ht.plan = rt.plan;
-  std::vector<int64_t> left;
+  std::vector<size_t> again;   // entries of left
   for (size_t t = 0; t < rt.inst.size(); ++t) {
     const int b = rt.inst[t];
     if (infos[b].iters <= at) continue;
-    if (rt.rank[t] == 0) left.push_back(b);
+    const bool kept = snaps && at % ce == 0 && infos[b].iters - at <= kSnaps * ce;
+    if (rt.rank[t] == 0) {
+      if (kept) {
+        const double* o = D(osn[b]) + (size_t)(at / ce % kSnaps) * snap_doubles(b);
+        double sc[2];
+        HIPCHK(hipMemcpyAsync(sc, o + 2 * n_b[b] + nr, 16, hipMemcpyDeviceToHost, hs));
+        HIPCHK(hipStreamSynchronize(hs));
+        left.push_back({b, o, o + n_b[b], sc[0], (int64_t)sc[1]});
+      } else {
+        again.push_back(left.size());
+        left.push_back({b, nullptr, nullptr, 0.0, 0});
+      }
+    }
+    if (kept) continue;
     ht.inst.push_back(b);
     ht.rank.push_back(rt.rank[t]);
   }
   if (left.empty()) return worst;
-  ht.grid = (int)std::min<size_t>(ht.inst.size(), (size_t)cus);
-  for (size_t j = 0; j < left.size(); ++j) {
-    const int64_t b = left[j];
-    hS[b].w_out = D(ohw) + j * n_max;
-    hS[b].y_out = D(ohy) + j * (nr + n_max);
-    hCt[b].stop_at = at;
-    HIPCHK(fill(D(oxb) + xoff[b], (xoff[b + 1] - xoff[b]) * 8, 0u, hs));
-    HIPCHK(fill(D(obar) + boff[b], (boff[b + 1] - boff[b]) * 8, 0u, hs));
-  }
-  HIPCHK(fill(Bd + onext, 4, 0u, hs));
-  HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
-  HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
-  if (ffo_status st = launch_reg_teams(ht, Bd + oP, Bd + oS, Bd + oCt, Bd + oteam, Bd + orank, Bd + onext, Hb + hteam_o,
-                                       Hb + hrank_o, stream))
-    return st;
-  HIPCHK(hipMemcpyAsync(hinfo, Bd + oinfo, (size_t)B * ffo::INFO_LEN * 8, hipMemcpyDeviceToHost, hs));
-  HIPCHK(hipMemcpyAsync(hstat, Bd + ostat, (size_t)B * 4, hipMemcpyDeviceToHost, hs));
-  HIPCHK(hipStreamSynchronize(hs));
-  for (size_t j = 0; j < left.size(); ++j) {
-    const int64_t b = left[j];
-    const double* h = hinfo + (size_t)b * ffo::INFO_LEN;
-    if (hstat[b] != ffo::DS_NOT_CONVERGED || (int64_t)h[ffo::IX_ITERS] != at)
-      return fail(FFO_EDEVICE, "a team ended without a result (bounded wait expired)");
-    if (ffo_status st = finish_plain(b, n_b[b], offs[b], n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d, GMV,
-                                     lambda1, lambda2, lambda3, opt, D(ohw) + j * n_max, D(ohy) + j * (nr + n_max),
-                                     h[ffo::IX_OMEGA], at, (int64_t)h[ffo::IX_RESTARTS], D(ohA), hs, w_out, &infos[b]))
+  if (!again.empty()) {
+    ht.grid = (int)std::min<size_t>(ht.inst.size(), (size_t)cus);
+    for (size_t j = 0; j < again.size(); ++j) {
+      const int64_t b = left[again[j]].b;
+      hS[b].w_out = D(ohw) + j * n_max;
+      hS[b].y_out = D(ohy) + j * (nr + n_max);
+      hCt[b].stop_at = at;
+      HIPCHK(fill(D(oxb) + xoff[b], (xoff[b + 1] - xoff[b]) * 8, 0u, hs));
+      HIPCHK(fill(D(obar) + boff[b], (boff[b + 1] - boff[b]) * 8, 0u, hs));
+    }
+    HIPCHK(fill(Bd + onext, 4, 0u, hs));
+    HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
+    HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
+    if (ffo_status st = launch_reg_teams(ht, Bd + oP, Bd + oS, Bd + oCt, Bd + oteam, Bd + orank, Bd + onext, Hb + hteam_o,
+                                         Hb + hrank_o, stream))
       return st;
+    HIPCHK(hipMemcpyAsync(hinfo, Bd + oinfo, (size_t)B * ffo::INFO_LEN * 8, hipMemcpyDeviceToHost, hs));
+    HIPCHK(hipMemcpyAsync(hstat, Bd + ostat, (size_t)B * 4, hipMemcpyDeviceToHost, hs));
+    HIPCHK(hipStreamSynchronize(hs));
+    for (size_t j = 0; j < again.size(); ++j) {
+      Left& l = left[again[j]];
+      const double* h = hinfo + (size_t)l.b * ffo::INFO_LEN;
+      if (hstat[l.b] != ffo::DS_NOT_CONVERGED || (int64_t)h[ffo::IX_ITERS] != at)
+        return fail(FFO_EDEVICE, "a team ended without a result (bounded wait expired)");
+      l.w = D(ohw) + j * n_max;
+      l.y = D(ohy) + j * (nr + n_max);
+      l.omega = h[ffo::IX_OMEGA];
+      l.restarts = (int64_t)h[ffo::IX_RESTARTS];
+    }
   }
+  for (const Left& l : left)
+    if (ffo_status st = finish_plain(l.b, n_b[l.b], offs[l.b], n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d,
+                                     GMV, lambda1, lambda2, lambda3, opt, l.w, l.y, l.omega, at, l.restarts, D(ohA), hs,
+                                     w_out, &infos[l.b]))
+      return st;
   HIPCHK(hipEventRecord(ws->ev[2], hs));
   HIPCHK(hipEventSynchronize(ws->ev[2]));
   hipEventElapsedTime(&ms_iter, ws->ev[1], ws->ev[2]);

@@ -65,6 +65,7 @@ struct DevState {
   int32_t* status;                    // [1]
   double* w_out;                      // [P][n] unscaled solution
   double* y_out;                      // optional dual output
+  double* snaps;                      // optional [ctl.snaps][2 n + nr + 2] iterates at checks (row-register kernel)
   const double* w_init;               // optional [P][n] unscaled starting weights (else w0)
   const double* y_init;               // optional unscaled starting duals, y_out layout (else 0)
 };
@@ -89,6 +90,8 @@ struct DevControl {
                         // float, as the FP32 form's copies in LDS are
   int64_t stop_at;      // row-register kernel: > 0 stops after that many iterations (a multiple of
                         // check_every) and writes the iterate itself, not T(z), to w_out and y_out
+  int32_t snaps;        // row-register kernel: > 0 keeps the iterates after the last `snaps` checks, that of check j
+                        // at snaps + (j % snaps)(2 n + nr + 2): weights, unscaled duals, primal weight, restarts
 };
 
 // Breakpoint lists: per workgroup and period, a count and LIST_CAP entries

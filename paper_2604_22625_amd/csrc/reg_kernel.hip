@@ -722,6 +722,14 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
         }
         ++it;
         __syncthreads();
+        if (check && cp->snaps) {
+          const auto [tid, lane, wave, rg, slot, li, val, mine, rown] = place<CA>(tid0, nwa, nr);
+          const long long j = it / cp->check_every;
+          double* o = opaque(sp)->snaps + (size_t)(j % cp->snaps) * (2 * n + nr + 2);
+          if (mine) { o[i0 + li] = dc * x; o[n + nr + i0 + li] = yc; }
+          if (wg == 0 && rown) o[n + tid] = L.dr[tid] * L.y[tid];
+          if (wg == 0 && tid == 0) { o[2 * n + nr] = omega; o[2 * n + nr + 1] = (double)L.restarts; }
+        }
         if (check && it == cp->stop_at) {   // hand the iterate over, unscaled, as a warm start
           const auto [tid, lane, wave, rg, slot, li, val, mine, rown] = place<CA>(tid0, nwa, nr);
           const DevState& s = *opaque(sp);
