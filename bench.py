@@ -175,8 +175,10 @@ def paper_grid(ff, torch, a):
             "rows": rows}
 
 
-def algorithmic_bytes_per_iter(n, k, m, P, Tp, w=8):
-    return 2 * (m + k) * n * w + n * (4 * P + 5 * Tp + 3) * w
+def algorithmic_bytes_per_iter(n, k, m, P, Tp, w=8, readings=2):
+    """The streaming model of an iteration: the rows for each product (readings = 1 where one
+    pass over rows in device memory serves both), and the state."""
+    return readings * (m + k) * n * w + n * (4 * P + 5 * Tp + 3) * w
 
 
 def cpu_baseline(inst, tol, max_iter, reps=3):
@@ -406,7 +408,7 @@ def stress_leg(ff, torch, n, steps=1, warmup=1, tol=1e-6, precision="fp64", ref=
     infos = [ff.solve_instance(d, tol=tol, out=W, time_limit_s=300, precision=precision)[1] for _ in range(steps)]
     torch.cuda.synchronize()
     w = 8 if precision == "fp64" else 4
-    bpi = algorithmic_bytes_per_iter(n, 60, 80, 1, 1, w=w)
+    bpi = algorithmic_bytes_per_iter(n, 60, 80, 1, 1, w=w, readings=1)
     iters = float(np.mean([i.iters for i in infos]))
     kms = float(np.mean([i.ms_iter for i in infos]))
     out = {"n": n, "k": 60, "m": 80, "precision": precision, "iters": iters, "kernel_ms": kms,
@@ -539,8 +541,8 @@ def main():
                    "n": n, "k": k, "m": m, "T": T, "instances_per_step": len(insts), "tol": a.tol},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "note": "achieved = algorithmic bytes (streaming model) / kernel time; the constraint slice "
-                             "and state stay in LDS, so HBM is nearly idle (traffic, counter-measured, is the "
+                     "note": "achieved = algorithmic bytes (streaming model) / kernel time; the constraint rows "
+                             "and state stay in registers and LDS, so HBM is nearly idle (traffic, counter-measured, is the "
                              "DRAM rate) and the iteration is limited by the latency of the per-iteration "
                              "exchange between workgroups, not by bandwidth"},
         "iters_mean": float(iters.mean()),
