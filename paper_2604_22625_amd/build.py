@@ -8,6 +8,8 @@ import os
 import shutil
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -25,26 +27,34 @@ def hipcc() -> str:
 
 
 def flags() -> list[str]:
-    return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
             # packed FP32 instructions stay off for every kernel of this library
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include")]
 
 
 def build(verbose: bool = False) -> str:
-    srcs = [os.path.join(CSRC, s) for s in SOURCES]
     tmp = LIB + ".tmp"
     # a failed build must not leave an older library behind to be loaded by mistake
     if os.path.exists(LIB):
         os.remove(LIB)
-    cmd = [hipcc()] + flags() + ["-o", tmp] + srcs
+    with tempfile.TemporaryDirectory() as objs:
+        out = [os.path.join(objs, s + ".o") for s in SOURCES]
+        # one compiler per source, all at once: the templates of three sources take minutes each
+        with ThreadPoolExecutor(min(len(SOURCES), os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda so: _run([hipcc()] + flags() + ["-c", os.path.join(CSRC, so[0]), "-o", so[1]], verbose),
+                          zip(SOURCES, out)))
+        _run([hipcc(), f"--offload-arch={ARCH}", "-fPIC", "-shared", "-o", tmp] + out, verbose)
+    os.replace(tmp, LIB)
+    return LIB
+
+
+def _run(cmd, verbose) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
-    os.replace(tmp, LIB)
-    return LIB
 
 
 if __name__ == "__main__":
