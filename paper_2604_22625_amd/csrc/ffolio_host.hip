@@ -291,6 +291,9 @@ __global__ void k_fill(uint32_t* p, int64_t words, uint32_t value) {
 // word.  Below 32 workgroups the extra reads of the copies cost more than they save.
 int xgroups_for(int nwg) { return nwg >= 32 ? ffo::XG_MAX : 1; }
 
+// The device clock now, for a time limit that spans several teams.
+__global__ void k_clock(long long* c) { *c = wall_clock64(); }
+
 // Default workgroup count of the plain and adjoint kernels: every phase of an iteration
 // is a latency chain, and with the grouped exchange its cost grows slowly with the grid,
 // so from n = 2000 on each workgroup takes 16 assets (up to one per compute unit);
@@ -724,25 +727,32 @@ constexpr int64_t kHandoff = 4;
 // of every instance: the longest of 256 ran 17 checks past the hand-off.
 constexpr int64_t kSnaps = 32;
 
+// Seconds of host time since `t`.
+double since(std::chrono::steady_clock::time_point t) {
+  return std::chrono::duration<double>(std::chrono::steady_clock::now() - t).count();
+}
+
 // Finishes instance b (n_b assets at offset o of the packed vectors) on the plain solve from
-// the iterate (w, y) after `it` iterations; rows: scratch for its m exposure rows.
+// the iterate (w, y) after `it` iterations, within `seconds`; rows: scratch for its m exposure
+// rows; w_out: its weights.
 ffo_status finish_plain(int64_t b, int64_t nb, int64_t o, int64_t n_max, int64_t k, int64_t m, const double* F,
                         const double* Omega, const double* delta, const double* A, const double* alpha,
                         const double* s, const double* q, const double* w0, const double* L, const double* U, double d,
                         double GMV, double lambda1, double lambda2, double lambda3, const ffo_options& opt,
-                        const double* w, const double* y, double omega, int64_t it, int64_t restarts, double* rows,
-                        hipStream_t st, double* w_out, ffo_info* info) {
+                        const double* w, const double* y, double omega, int64_t it, int64_t restarts, double seconds,
+                        double* rows, hipStream_t st, double* w_out, ffo_info* info) {
   if (m > 0)
     HIPCHK(hipMemcpy2DAsync(rows, (size_t)nb * 8, A, (size_t)n_max * 8, (size_t)nb * 8, (size_t)m,
                             hipMemcpyDeviceToDevice, st));
   ffo_options o2 = opt;
   o2.max_iter = std::max<int64_t>(1, opt.max_iter - it);
+  o2.time_limit_s = seconds;
   o2.workgroups = 0;
   o2.verbose = 0;
   *info = ffo_info{};
   const ffo_status sb = solve_impl(nb, k, m, 0, alpha + o, F, Omega, delta, s + o, q + o, d, rows,
                                    m ? L + (size_t)b * m : nullptr, m ? U + (size_t)b * m : nullptr, w0 + o, GMV, lambda1,
-                                   lambda2, lambda3, nullptr, w, y, omega, &o2, st, w_out + o, nullptr, info, nullptr);
+                                   lambda2, lambda3, nullptr, w, y, omega, &o2, st, w_out, nullptr, info, nullptr);
   if (sb == FFO_EINVAL || sb == FFO_ENOMEM || sb == FFO_EDEVICE) return sb;
   info->iters += it;
   info->restarts += restarts;
@@ -942,6 +952,7 @@ ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_
 
   // ---- the solve: start, then replays of one checked graph ----
   HIPCHK(hipEventRecord(ws->ev[1], ps));
+  const auto begin = std::chrono::steady_clock::now();
   HIPCHK(ls_start(S, tu, gA, gC, hact, hcnt, ps));
   hipGraphExec_t ex = nullptr;
   HIPCHK(ls_graph(S, tu, gA, gC, ce, true, ps, &ex));
@@ -973,9 +984,11 @@ ffo_status batched_lockstep(int64_t B, const int64_t* n_b, int64_t n_max, int64_
       const ffo::LsInst I = hinst[b];
       if (ffo::ls_launch_export(S, (int)b, (int)nb, D(ohw), D(ohy), ps)) return fail(FFO_EDEVICE, "export launch failed");
       ffo_info ib{};
+      // (past the limit: one check interval, which returns the iterate as FFO_TIMEOUT)
+      const double rest = std::max(opt.time_limit_s - since(begin), 1e-9);
       if (ffo_status sb = finish_plain(b, nb, o, n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d, GMV, lambda1,
-                                       lambda2, lambda3, opt, D(ohw), D(ohy), I.omega, I.it, I.restarts, D(ohA), ps,
-                                       w_out, &ib))
+                                       lambda2, lambda3, opt, D(ohw), D(ohy), I.omega, I.it, I.restarts, rest, D(ohA),
+                                       ps, w_out + o, &ib))
         return sb;
       handed.emplace_back(b, ib);
     }
@@ -1677,10 +1690,11 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t oP = carve(B, sizeof(ffo::DevProblem)), oS = carve(B, sizeof(ffo::DevState));
   const size_t nslot = std::max<size_t>(W, rt.inst.size());
   const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(nslot, 4), orank = carve(nslot, 4), onext = carve(1, 4);
-  // the hand-off of the last instances: their iterates and one copy of exposure rows
+  const size_t oclk = carve(1, 8);
+  // the hand-off of the last instances: their iterates, one copy of exposure rows, one result
   const int64_t hand = as_lockstep && B > kHandoff ? kHandoff : 0;
   const size_t ohw = carve(hand ? (size_t)hand * n_max : 1, 8), ohy = carve(hand ? (size_t)hand * (nr + n_max) : 1, 8);
-  const size_t ohA = carve(hand ? (size_t)std::max<int64_t>(m, 1) * n_max : 1, 8);
+  const size_t ohA = carve(hand ? (size_t)std::max<int64_t>(m, 1) * n_max : 1, 8), ohx = carve(hand ? n_max : 1, 8);
   // every instance's iterates after its last kSnaps checks, unless they take over 1 GiB
   const auto snap_doubles = [&](int64_t b) { return (size_t)(2 * n_b[b] + nr + 2); };
   const bool snaps = hand && (2 * N + B * (nr + 2)) * kSnaps * 8 <= (int64_t)1 << 30;
@@ -1766,6 +1780,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     sv.xbuf = D(oxb) + xoff[b]; sv.bar = (unsigned long long*)(Bd + obar) + boff[b];
     sv.info = D(oinfo) + (size_t)b * ffo::INFO_LEN; sv.status = (int32_t*)(Bd + ostat) + b;
     sv.w_out = w_out + o; sv.y_out = nullptr;
+    if (as_lockstep) sv.clock0 = (const long long*)(Bd + oclk);   // one clock for the call, as in that form
     hS[b] = sv;
     ffo::DevControl c = c0;
     c.nwg = g[b];
@@ -1786,6 +1801,10 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
   HIPCHK(hipEventRecord(ws->ev[1], hs));
+  if (as_lockstep) {
+    hipLaunchKernelGGL(k_clock, dim3(1), dim3(1), 0, hs, (long long*)(Bd + oclk));
+    HIPCHK(hipGetLastError());
+  }
   if (ffo_status st = reg ? launch_reg_teams(rt, Bd + oP, Bd + oS, Bd + oCt, Bd + oteam, Bd + orank, Bd + onext, Hb + hteam_o,
                                              Hb + hrank_o, stream)
                           : launch_teams(tp, W, ckl, csl, clds, prec, (const ffo::DevProblem*)(Bd + oP),
@@ -1799,6 +1818,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   HIPCHK(hipMemcpyAsync(hinfo, Bd + oinfo, (size_t)B * ffo::INFO_LEN * 8, hipMemcpyDeviceToHost, hs));
   HIPCHK(hipMemcpyAsync(hstat, Bd + ostat, (size_t)B * 4, hipMemcpyDeviceToHost, hs));
   HIPCHK(hipStreamSynchronize(hs));
+  const auto ended = std::chrono::steady_clock::now();
   float ms_setup = 0.f, ms_iter = 0.f;
   hipEventElapsedTime(&ms_setup, ws->ev[0], ws->ev[1]);
   hipEventElapsedTime(&ms_iter, ws->ev[1], ws->ev[2]);
@@ -1809,13 +1829,17 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
                  (long long)B, reg ? 1 : chunks.size(), reg ? rt.grid : W, occ, lds_cap, reg ? 2 : ckl[0], reg ? 2 : csl[0],
                  reg ? 0 : clds[0], ms_setup, ms_iter);
   ffo_status worst = collect_teams(B, n_b, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
-  if (!hand || worst == FFO_EDEVICE) return worst;
+  const bool expired = std::any_of(infos, infos + B, [](const ffo_info& i) { return i.status == FFO_TIMEOUT; });
+  if (!hand || worst == FFO_EDEVICE || expired) return worst;
+  const double used = ms_iter * 1e-3;
+  const auto rest = [&]() { return opt.time_limit_s - used - since(ended); };   // of the call's time limit
 
   // ---- the lockstep form's hand-off: there, at the first check that leaves at most
   // kHandoff instances, these go on as warm-started plain solves.  That check is the
   // iteration count of the (kHandoff + 1)-th longest solve.  The longer ones go on from their
   // iterates there; those that ran more than kSnaps checks past it, or kept none, run again up
-  // to it first (the same iterations, all of them side by side).
+  // to it first (the same iterations, all of them side by side).  The time limit is the call's:
+  // an instance whose continuation it ends keeps the result of its team.
   std::vector<int64_t> its(B);
   for (int64_t b = 0; b < B; ++b) its[b] = infos[b].iters;
   std::nth_element(its.begin(), its.begin() + kHandoff, its.end(), std::greater<int64_t>());
@@ -1868,6 +1892,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     for (size_t j = 0; j < again.size(); ++j) {
       Left& l = left[again[j]];
       const double* h = hinfo + (size_t)l.b * ffo::INFO_LEN;
+      if (hstat[l.b] == ffo::DS_TIMEOUT) continue;
       if (hstat[l.b] != ffo::DS_NOT_CONVERGED || (int64_t)h[ffo::IX_ITERS] != at)
         return fail(FFO_EDEVICE, "a team ended without a result (bounded wait expired)");
       l.w = D(ohw) + j * n_max;
@@ -1876,11 +1901,19 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
       l.restarts = (int64_t)h[ffo::IX_RESTARTS];
     }
   }
-  for (const Left& l : left)
+  for (const Left& l : left) {
+    const double seconds = rest();
+    if (seconds <= 0.0) break;
+    if (!l.w) continue;
+    ffo_info ib{};
     if (ffo_status st = finish_plain(l.b, n_b[l.b], offs[l.b], n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d,
-                                     GMV, lambda1, lambda2, lambda3, opt, l.w, l.y, l.omega, at, l.restarts, D(ohA), hs,
-                                     w_out, &infos[l.b]))
+                                     GMV, lambda1, lambda2, lambda3, opt, l.w, l.y, l.omega, at, l.restarts, seconds,
+                                     D(ohA), hs, D(ohx), &ib))
       return st;
+    if (ib.status == FFO_TIMEOUT) continue;
+    infos[l.b] = ib;
+    HIPCHK(hipMemcpyAsync(w_out + offs[l.b], D(ohx), (size_t)n_b[l.b] * 8, hipMemcpyDeviceToDevice, hs));
+  }
   HIPCHK(hipEventRecord(ws->ev[2], hs));
   HIPCHK(hipEventSynchronize(ws->ev[2]));
   hipEventElapsedTime(&ms_iter, ws->ev[1], ws->ev[2]);

@@ -551,7 +551,8 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
             L.sc[5][tid] = mine ? conj15(ty, ca, cb, d) : 0.0;
             L.sc[6][tid] = mine ? ty * w0 : 0.0;
             L.sc[7][tid] = h;
-            L.sc[8][tid] = wg == 0 && tid == 0 && (double)(wall_clock64() - t_start) / ctl.wall_hz > ctl.time_limit_s;
+            L.sc[8][tid] = wg == 0 && tid == 0 &&
+                           (double)(wall_clock64() - (s.clock0 ? *s.clock0 : t_start)) / ctl.wall_hz > ctl.time_limit_s;
             L.sc[9][tid] = mine ? (isfinite(tx) ? 0.0 : 1.0) + (isfinite(ty) ? 0.0 : 1.0) : 0.0;
             L.sc[10][tid] = ex;
             L.sc[11][tid] = mine ? fabs(w) : 0.0;
