@@ -1838,8 +1838,9 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   // kHandoff instances, these go on as warm-started plain solves.  That check is the
   // iteration count of the (kHandoff + 1)-th longest solve.  The longer ones go on from their
   // iterates there; those that ran more than kSnaps checks past it, or kept none, run again up
-  // to it first (the same iterations, all of them side by side).  The time limit is the call's:
-  // an instance whose continuation it ends keeps the result of its team.
+  // to it first (the same iterations, all of them side by side).  An instance keeps the result of
+  // its team where its continuation runs into the call's time limit, or converges no more within
+  // max_iter (a restart from the iterate alone takes up to half as many iterations again).
   std::vector<int64_t> its(B);
   for (int64_t b = 0; b < B; ++b) its[b] = infos[b].iters;
   std::nth_element(its.begin(), its.begin() + kHandoff, its.end(), std::greater<int64_t>());
@@ -1892,9 +1893,10 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     for (size_t j = 0; j < again.size(); ++j) {
       Left& l = left[again[j]];
       const double* h = hinfo + (size_t)l.b * ffo::INFO_LEN;
-      if (hstat[l.b] == ffo::DS_TIMEOUT) continue;
-      if (hstat[l.b] != ffo::DS_NOT_CONVERGED || (int64_t)h[ffo::IX_ITERS] != at)
+      if (status_of(hstat[l.b]) == FFO_EDEVICE)
         return fail(FFO_EDEVICE, "a team ended without a result (bounded wait expired)");
+      // (ended by its tolerance or the time limit instead: the sums may come in another order)
+      if (hstat[l.b] != ffo::DS_NOT_CONVERGED || (int64_t)h[ffo::IX_ITERS] != at) continue;
       l.w = D(ohw) + j * n_max;
       l.y = D(ohy) + j * (nr + n_max);
       l.omega = h[ffo::IX_OMEGA];
@@ -1910,7 +1912,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
                                      GMV, lambda1, lambda2, lambda3, opt, l.w, l.y, l.omega, at, l.restarts, seconds,
                                      D(ohA), hs, D(ohx), &ib))
       return st;
-    if (ib.status == FFO_TIMEOUT) continue;
+    if (ib.status == FFO_TIMEOUT || (ib.status != FFO_OK && infos[l.b].status == FFO_OK)) continue;
     infos[l.b] = ib;
     HIPCHK(hipMemcpyAsync(w_out + offs[l.b], D(ohx), (size_t)n_b[l.b] * 8, hipMemcpyDeviceToDevice, hs));
   }

@@ -1,5 +1,6 @@
 """GPU: the limits of a batched call.  The default form's time limit is the call's, as in the
-lockstep form it stands in for, whatever the number of instances that wait for a compute unit."""
+lockstep form it stands in for, whatever the number of instances that wait for a compute unit,
+and an instance that converged within max_iter stays converged."""
 import pytest
 
 from synth import make_batch
@@ -52,3 +53,22 @@ def test_instances_that_converged_in_time_keep_their_results():
             continue
         o, e = int(batch["offs"][j]), int(batch["offs"][j + 1])
         assert b[j].iters == a[j].iters and float((Wc[o:e] - W[o:e]).abs().max()) <= 1e-10 * float(W[o:e].abs().max())
+
+
+@pytest.mark.parametrize("check_every,seed,j", [(64, 19, 0), (4, 14, 3)])   # iterates kept, and a second run
+def test_hand_off_keeps_a_converged_result(check_every, seed, j):
+    """Instance j, of the four that a hand-off continues, takes more iterations from there than its
+    team did: with the team's count as the limit the team's result is the answer."""
+    ff = _ff()
+    batch = make_batch(6, 6, 5, seed=seed, n_lo=40, n_hi=400)
+    print(f"[case] converged hand-off check_every={check_every}", flush=True)
+    kw = dict(tol=1e-7, check_every=check_every, time_limit_s=20.0, raise_on_failure=False)
+    Wt, t = ff.solve_batched(batch, form="teams", max_iter=100_000, **kw)
+    cut = t[j].iters
+    W, a = ff.solve_batched(batch, max_iter=cut, **kw)
+    assert ff.solve_batched(batch, max_iter=100_000, **kw)[1][j].iters > cut
+    for b, (i, it) in enumerate(zip(a, t)):     # (a hand-off may also converge earlier than the team)
+        assert i.status == 0 or it.iters > cut, (b, i)
+    o, e = int(batch["offs"][j]), int(batch["offs"][j + 1])
+    assert a[j].iters == cut and a[j].rel_kkt <= 1e-7
+    assert float((W[o:e] - Wt[o:e]).abs().max()) <= 1e-10 * float(Wt[o:e].abs().max())
