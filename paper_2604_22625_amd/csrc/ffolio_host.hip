@@ -1162,6 +1162,17 @@ struct RegTeams {
   int grid = 0;
 };
 
+// Whether N assets in all, with nr rows, are faster in the lockstep form: its matrix products
+// take less time per asset than the teams' chains, once there is enough to do to cover its launches.
+// Lockstep and teams, to the default tolerance: 140 rows 442 and 417 ms at N = 987,000 (n 1000 to
+// 8000), 491 and 567 at 1,024,000 and 577 and 714 at 1,280,000 (n = 8000); 70 rows 668 and 617 at
+// 2,000,000, 871 and 945 at 2,880,000, 1169 and 1278 at 4,000,000 (n = 8000); 40 rows 1004 and 909
+// at 3,200,000, 1770 and 1753 at 6,400,000; 10 rows 1278 and 1053 at 4,000,000, 3003 and 3244 at
+// 8,000,000 (n = 16,000).  (256 instances, n 500 to 8000, 70 rows, 720,000: 375 and 184.)
+bool lockstep_faster(int64_t N, int nr, int cus) {
+  return N > (int64_t)cus * (nr > 80 ? 4000 : nr > 48 ? 11000 : 25000);
+}
+
 bool plan_reg_teams(int64_t B, const int64_t* n_b, int nr, int64_t T, bool prec_ok, double d, const ffo_options& opt,
                     int cus, RegTeams* out) {
   if (T != 0 || !prec_ok || opt.speculative == 0 || opt.verbose >= 2 || !(d == 1.5 || d == 2.0)) return false;
@@ -1617,11 +1628,10 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const int prec = opt.precision == FFO_FP32 ? ffo::PREC_FP32
                    : (opt.precision == FFO_FP32_BF16K ? ffo::PREC_BF16K : ffo::PREC_FP64);
   // The row-register teams where they apply; unless a form is asked for they also stand in
-  // for the lockstep form, with its results (256 instances, n 500 to 8000, 70 rows: 385 ms
-  // in lockstep, 171 here).  deterministic keeps the lockstep form, whose sums have a
-  // fixed order.
+  // for the lockstep form, with its results, up to a number of assets in all.  deterministic
+  // keeps the lockstep form, whose sums have a fixed order.
   RegTeams rt;
-  const bool reg = opt.batched_form != 2 && !(lockstep && opt.deterministic) && 
+  const bool reg = opt.batched_form != 2 && !(lockstep && (opt.deterministic || lockstep_faster(N, nr, cus))) &&
                    plan_reg_teams(B, n_b, nr, 0, prec == ffo::PREC_FP64, d, opt, cus, &rt);
   const bool as_lockstep = lockstep && reg;
   if (lockstep && !reg)
