@@ -470,7 +470,8 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   size_t off = 0;
   auto carve = [&](size_t cnt, size_t elt) { const size_t o = off; off = align_up(off + cnt * elt); return o; };
   const size_t oK = carve((size_t)std::max(nr, 1) * ldk, 8), odr = carve(std::max(nr, 1), 8), odc = carve(n, 8);
-  const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k && !reg;   // FP32 form reading rows from device memory
+  // FP32 form reading rows from device memory (the tiles are floats already)
+  const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k && !reg && !tile_bytes;
   const size_t oKf = carve(f32rows ? (size_t)std::max(nr, 1) * ldk : 1, 4);
   const size_t oKt = carve(tile_bytes, 1);
   const size_t odrC = carve(Tpn, 8), oar = carve(n, 8), ocv = carve(n, 8), oca = carve(Tpn, 8), ocb = carve(Tpn, 8);

@@ -29,7 +29,7 @@ struct DevProblem {
   int32_t n, k, m, P, Tp, nr, multi, ldk;
   int32_t kscaled;      // 1: K holds diag(dr) K diag(dc); 0: K holds K diag(dc), rows scaled by dr on use
   const double* K;      // [nr][ldk] constraint rows (see kscaled)
-  const float* Kf;      // the same rows rounded to float (FP32 form reading rows from device memory), or null
+  const float* Kf;      // the same rows rounded to float (FP32 form with rows in device memory, not in tiles), or null
   const void* Kt;       // the same rows in tiles, double or float, for the one-pass form (launch_blocks), or null
   const uint16_t* Kb;   // the same rows as bfloat16 bit patterns (PREC_BF16K), or null
   const double* dr;     // [nr]

@@ -55,6 +55,15 @@ def test_impact_exponents(capfd, d, kernel):
     assert _summary(capfd, make_single(300, 6, 5, seed=2, d=d))["kernel"] == kernel
 
 
+def test_tiles_need_no_second_float_copy(capfd):
+    """FP32 rows in tiles: the workspace holds the rows as doubles and the tiles, and less than a
+    third copy (nr x n floats) besides: fifteen vectors, the breakpoint lists, an exchange slot."""
+    n, k, m = 70_000, 60, 80
+    f = _summary(capfd, make_single(n, k, m, seed=4), precision="fp32")
+    rows, tiles = (k + m) * 8 * (n + 63), 144 * 4 * (n + 256 * 16)
+    assert f["kernel"] == "tiles" and int(f["workspace"]) < rows + tiles + 25_000_000
+
+
 @pytest.mark.parametrize("B,line", [(100, "[ffo batch]"), (132, "[ffo lockstep]")])
 def test_large_batches_take_the_lockstep_form(capfd, B, line):
     """100 rows: teams up to 4000 assets per compute unit (256 of them), lockstep beyond."""
