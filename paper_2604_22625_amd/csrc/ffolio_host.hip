@@ -56,15 +56,20 @@ ffo_status get_workspace(int dev, void* stream, size_t bytes, size_t host_bytes,
     if (w.base) hipFree(w.base);
     w.base = nullptr;
     w.bytes = 0;
-    if (hipMalloc(&w.base, bytes) != hipSuccess) return fail(FFO_ENOMEM, "hipMalloc of the solver workspace failed");
+    if (hipMalloc(&w.base, bytes) != hipSuccess) {
+      (void)hipGetLastError();   // reported here, not by the next launch
+      return fail(FFO_ENOMEM, "hipMalloc of the solver workspace failed");
+    }
     w.bytes = bytes;
   }
   if (w.host_bytes < host_bytes) {
     if (w.host) hipHostFree(w.host);
     w.host = nullptr;
     w.host_bytes = 0;
-    if (hipHostMalloc(&w.host, host_bytes, hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc(&w.host, host_bytes, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
       return fail(FFO_ENOMEM, "hipHostMalloc of the staging buffer failed");
+    }
     w.host_bytes = host_bytes;
   }
   for (auto& e : w.ev)
@@ -450,10 +455,12 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   const bool mpk = T > 0 && c.prec == ffo::PREC_FP64 && !opt.deterministic && opt.workgroups == 0 && opt.speculative <= 0 &&
                    opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::mp_plan(n, nr, (int)P, cus, lds_cap, &mp);
   // Single-period slices whose rows do not fit in LDS read them once per iteration, in tiles
-  // (a second copy of the rows: not beyond 8 GiB of it, nor in the fixed scratch of the
-  // allocation-free entry).  FP32, 140 rows, per iteration: rows in LDS 33 us at n = 50,000 and
+  // (a second copy of the rows: not beyond 8 GiB of it, nor where the device has no room for it,
+  // nor in the fixed scratch of the allocation-free entry).  FP32, 140 rows, per iteration: rows in LDS 33 us at n = 50,000 and
   // 39 at 60,000; tiles 41 at 70,000 and 47 at 100,000, where rows read twice took 96.
   size_t tile_bytes = 0;
+  const ffo::DevControl two_pass = c;
+  const size_t two_pass_lds = lds;
   if (!reg && !mpk && !fx && T == 0 && c.spec && !c.lds_k) {
     ffo::DevControl t = c;
     t.stream = ffo::stream_rows(nr);
@@ -470,10 +477,6 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   size_t off = 0;
   auto carve = [&](size_t cnt, size_t elt) { const size_t o = off; off = align_up(off + cnt * elt); return o; };
   const size_t oK = carve((size_t)std::max(nr, 1) * ldk, 8), odr = carve(std::max(nr, 1), 8), odc = carve(n, 8);
-  // FP32 form reading rows from device memory (the tiles are floats already)
-  const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k && !reg && !tile_bytes;
-  const size_t oKf = carve(f32rows ? (size_t)std::max(nr, 1) * ldk : 1, 4);
-  const size_t oKt = carve(tile_bytes, 1);
   const size_t odrC = carve(Tpn, 8), oar = carve(n, 8), ocv = carve(n, 8), oca = carve(Tpn, 8), ocb = carve(Tpn, 8);
   const size_t obF = carve(std::max<int64_t>(k, 1), 8), ocr = carve(1, 8), oC = carve(std::max<int64_t>(k * k, 1), 8);
   size_t ost[6];
@@ -484,7 +487,11 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   const size_t oxb = carve(nxbuf, 8), obar = carve(ffo::BAR_WORDS, 8);
   const size_t oblist = carve(c.lists ? (size_t)2 * nwg * P * ffo::LIST_W : 1, 8);
   const size_t oinfo = carve(ffo::INFO_LEN, 8), ostat = carve(1, 4), oflag = carve(1, 4);
-  const size_t total = off;
+  // last, the rows again: in tiles, or as floats for the FP32 form that reads them from device memory
+  const size_t oKx = off;
+  const bool f32rows = c.prec == ffo::PREC_FP32 && !c.lds_k && !reg;   // (unless in tiles, floats already)
+  const size_t f32_bytes = f32rows ? (size_t)std::max(nr, 1) * ldk * 4 : 0;
+  size_t total = oKx + align_up(tile_bytes ? tile_bytes : f32_bytes);
   // host staging: Omega, its factor, the factorisation's work space, info, two flags
   const size_t kk = (size_t)std::max<int64_t>(k * k, 1);
   size_t hoff = 0;
@@ -506,7 +513,16 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
     ev = fx->ev;
   } else {
     Workspace* ws = nullptr;
-    if (ffo_status st = get_workspace(dev, stream, total, host_bytes, &ws)) return st;
+    ffo_status st = get_workspace(dev, stream, total, host_bytes, &ws);
+    if (st == FFO_ENOMEM && tile_bytes) {
+      tile_bytes = 0;
+      c = two_pass;
+      lds = two_pass_lds;
+      total = oKx + align_up(f32_bytes);
+      st = get_workspace(dev, stream, total, host_bytes, &ws);
+      if (!st) g_err.clear();
+    }
+    if (st) return st;
     B = (char*)ws->base;
     H = (char*)ws->host;
     ev = ws->ev;
@@ -546,14 +562,13 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   p.cvec = D(ocv); p.ca = D(oca); p.cb = D(ocb); p.w0 = w0; p.wT = w_target; p.L = L; p.U = U;
   p.bF = D(obF); p.g1 = g1; p.d = d; p.g2 = g2;
   p.crisk = D(ocr);
-  if (f32rows) {
-    if (ffo::launch_to_float(D(oK), (float*)(B + oKf), (int64_t)nr * ldk, stream))
-      return fail(FFO_EDEVICE, "setup kernel launch failed");
-    p.Kf = (const float*)(B + oKf);
-  }
   if (tile_bytes) {
-    if (ffo::launch_blocks(p, c, B + oKt, stream)) return fail(FFO_EDEVICE, "setup kernel launch failed");
-    p.Kt = B + oKt;
+    if (ffo::launch_blocks(p, c, B + oKx, stream)) return fail(FFO_EDEVICE, "setup kernel launch failed");
+    p.Kt = B + oKx;
+  } else if (f32rows) {
+    if (ffo::launch_to_float(D(oK), (float*)(B + oKx), (int64_t)nr * ldk, stream))
+      return fail(FFO_EDEVICE, "setup kernel launch failed");
+    p.Kf = (const float*)(B + oKx);
   }
 
   ffo::DevState sv{};
@@ -1707,9 +1722,11 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const int64_t hand = as_lockstep && B > kHandoff ? kHandoff : 0;
   const size_t ohw = carve(hand ? (size_t)hand * n_max : 1, 8), ohy = carve(hand ? (size_t)hand * (nr + n_max) : 1, 8);
   const size_t ohA = carve(hand ? (size_t)std::max<int64_t>(m, 1) * n_max : 1, 8), ohx = carve(hand ? n_max : 1, 8);
-  // every instance's iterates after its last kSnaps checks, unless they take over 1 GiB
+  // every instance's iterates after its last kSnaps checks, unless they take over 1 GiB or the
+  // device has no room for them
+  const size_t base_bytes = off;
   const auto snap_doubles = [&](int64_t b) { return (size_t)(2 * n_b[b] + nr + 2); };
-  const bool snaps = hand && (2 * N + B * (nr + 2)) * kSnaps * 8 <= (int64_t)1 << 30;
+  bool snaps = hand && (2 * N + B * (nr + 2)) * kSnaps * 8 <= (int64_t)1 << 30;
   std::vector<size_t> osn(B, 0);
   if (snaps)
     for (int64_t b = 0; b < B; ++b) osn[b] = carve(snap_doubles(b) * kSnaps, 8);
@@ -1724,7 +1741,13 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t host_bytes = hoff;
 
   Workspace* ws = nullptr;
-  if (ffo_status st = get_workspace(dev, stream, total, host_bytes, &ws, 1)) return st;
+  ffo_status got = get_workspace(dev, stream, total, host_bytes, &ws, 1);
+  if (got == FFO_ENOMEM && snaps) {
+    snaps = false;
+    got = get_workspace(dev, stream, base_bytes, host_bytes, &ws, 1);
+    if (!got) g_err.clear();
+  }
+  if (got) return got;
   char* Bd = (char*)ws->base;
   char* Hb = (char*)ws->host;
   auto D = [&](size_t o) { return (double*)(Bd + o); };

@@ -1,0 +1,93 @@
+"""The host side's memory plans, without a GPU: the built library against a stand-in for the HIP
+calls (fake_hip.cpp), in a process of its own, in which kernels do nothing and every solve ends at
+once.  Checked is what the library allocates and what it does when that fails."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_2604_22625_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, json, os, sys
+sys.path.insert(0, {root!r})
+fake = ctypes.CDLL({fake!r}, mode=ctypes.RTLD_GLOBAL)
+fake.fake_log.restype = ctypes.c_char_p
+fake.fake_limit.argtypes = [ctypes.c_size_t]
+import paper_2604_22625_amd as ff
+L, p = ff.lib(), ctypes.c_void_p(0x1000)      # device arrays: never read
+
+def options(**kw):
+    o = ff.default_options()
+    for k, v in kw.items():
+        setattr(o, k, v)
+    return ctypes.byref(o)
+
+def solve(n, m, T=0, **kw):
+    return L.ffo_solve(n, 0, m, T, p, None, None, p, p, p, 1.5, p, p, p, p, 1e9, 1e-9, 1.0, 1.0, p if T else None,
+                       options(verbose=1, **kw), None, p, None, ctypes.byref(ff._Info()))
+
+def batched(sizes, m, **kw):
+    B = len(sizes)
+    nb, offs = (ctypes.c_int64 * B)(*sizes), (ctypes.c_int64 * (B + 1))(0)
+    for b in range(B):
+        offs[b + 1] = offs[b] + nb[b]
+    return L.ffo_solve_batched(B, nb, max(sizes), 0, m, None, None, p, p, offs, p, p, p, p, p, p, 1.5, 1e9, 1e-9, 1.0, 1.0,
+                               options(verbose=1, **kw), None, p, (ff._Info * B)())
+
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run([build.hipcc(), "-O1", "-fPIC", "-shared", "--offload-host-only", "-o", out, os.path.join(HERE, "fake_hip.cpp")],
+                   check=True, capture_output=True)
+    return out
+
+
+def _run(fake, body):
+    """The value of `out` that the body leaves, the stand-in's calls and the standard error."""
+    code = (PRELUDE.format(root=os.path.dirname(HERE), fake=fake) + body +
+            "\nprint(json.dumps([out, fake.fake_log().decode()]), flush=True)\nsys.stderr.flush()\nos._exit(0)\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    out, log = json.loads(r.stdout.splitlines()[-1])
+    return out, [(w, int(v)) for w, v in (line.split() for line in log.splitlines())], r.stderr
+
+
+@pytest.mark.parametrize("precision,floats", [(0, 0), (1, 1)])
+def test_solve_without_room_for_tiles(fake, precision, floats):
+    """n = 400,000, 60 rows: 192 MB of rows, about fifteen vectors, and the rows again in tiles
+    (80 of them, with the padding of a tile) or, in FP32 without tiles, as floats."""
+    out, log, err = _run(fake, f"""
+out = [solve(400_000, 60, precision={precision})]
+L.ffo_release()
+fake.fake_limit(350_000_000)
+out.append(solve(400_000, 60, precision={precision}))
+""")
+    sizes = [v for w, v in log if w == "malloc"]
+    assert out == [0, 0], err
+    assert [s.split()[0] for s in err.split("kernel ")[1:]] == ["tiles", "general"]
+    assert len(sizes) == 3 and sizes[0] == sizes[1] >= 350_000_000
+    rows, vectors = 60 * 400_000 * 8, 16 * 400_000 * 8
+    assert rows < sizes[2] < rows + vectors + floats * rows // 2 + 2_000_000
+
+
+def test_batch_without_room_for_iterates(fake):
+    """200 instances of 7500 assets: a dozen vectors of 1.5 million entries, and 32 copies of two
+    vectors for the hand-off."""
+    out, log, err = _run(fake, """
+out = [batched([7500] * 200, 10)]
+L.ffo_release()
+fake.fake_limit(600_000_000)
+out.append(batched([7500] * 200, 10))
+""")
+    sizes = [v for w, v in log if w == "malloc"]
+    assert out == [0, 0], err
+    assert len(sizes) == 3 and sizes[0] == sizes[1] > 64 * 1_500_000 * 8
+    assert sizes[2] < 13 * 1_500_000 * 8
