@@ -1715,7 +1715,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t oxb = carve(xoff[B], 8), obar = carve(boff[B], 8);
   const size_t oinfo = carve((size_t)B * ffo::INFO_LEN, 8), ostat = carve(B, 4), oflag = carve(1, 4);
   const size_t oP = carve(B, sizeof(ffo::DevProblem)), oS = carve(B, sizeof(ffo::DevState));
-  const size_t nslot = std::max<size_t>(W, rt.inst.size());
+  const size_t nslot = reg ? rt.inst.size() : W;   // entries of one launch's tables
   const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(nslot, 4), orank = carve(nslot, 4), onext = carve(1, 4);
   const size_t oclk = carve(1, 8);
   // the hand-off of the last instances: their iterates, one copy of exposure rows, one result
@@ -1737,7 +1737,8 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   const size_t hflag_o = hcarve(4), hinfo_o = hcarve((size_t)B * ffo::INFO_LEN * 8), hstat_o = hcarve((size_t)B * 4);
   const size_t hP_o = hcarve((size_t)B * sizeof(ffo::DevProblem)), hS_o = hcarve((size_t)B * sizeof(ffo::DevState));
   const size_t hCt_o = hcarve((size_t)B * sizeof(ffo::DevControl)), hnb_o = hcarve((size_t)B * 8);
-  const size_t hteam_o = hcarve(nslot * 4 * chunks.size()), hrank_o = hcarve(nslot * 4 * chunks.size());
+  const size_t launches = reg ? 1 : chunks.size();
+  const size_t hteam_o = hcarve(nslot * 4 * launches), hrank_o = hcarve(nslot * 4 * launches);
   const size_t host_bytes = hoff;
 
   Workspace* ws = nullptr;
@@ -1861,7 +1862,7 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     std::fprintf(stderr,
                  "[ffo batch] B %lld launches %zu resident %d (occupancy %d) lds %zu | first launch: slice in LDS %d, "
                  "state in LDS %d (2: registers), %zu bytes | setup %.3f ms solve %.3f ms\n",
-                 (long long)B, reg ? 1 : chunks.size(), reg ? rt.grid : W, occ, lds_cap, reg ? 2 : ckl[0], reg ? 2 : csl[0],
+                 (long long)B, launches, reg ? rt.grid : W, occ, lds_cap, reg ? 2 : ckl[0], reg ? 2 : csl[0],
                  reg ? 0 : clds[0], ms_setup, ms_iter);
   ffo_status worst = collect_teams(B, n_b, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
   const bool expired = std::any_of(infos, infos + B, [](const ffo_info& i) { return i.status == FFO_TIMEOUT; });
@@ -2077,7 +2078,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   const size_t oxb = carve(xoff[B], 8), obar = carve(boff[B], 8);
   const size_t oinfo = carve((size_t)B * ffo::INFO_LEN, 8), ostat = carve(B, 4), oflag = carve(1, 4);
   const size_t oP = carve(B, sizeof(ffo::DevProblem)), oS = carve(B, sizeof(ffo::DevState));
-  const size_t nslot = std::max<size_t>(W, rt.inst.size());
+  const size_t nslot = reg ? rt.inst.size() : W;   // entries of one launch's tables
   const size_t oCt = carve(B, sizeof(ffo::DevControl)), oteam = carve(nslot, 4), orank = carve(nslot, 4), onext = carve(1, 4);
   const size_t total = off;
   const size_t kk = (size_t)std::max<int64_t>(k * k, 1);
@@ -2087,7 +2088,8 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   const size_t hflag_o = hcarve(4), hinfo_o = hcarve((size_t)B * ffo::INFO_LEN * 8), hstat_o = hcarve((size_t)B * 4);
   const size_t hP_o = hcarve((size_t)B * sizeof(ffo::DevProblem)), hS_o = hcarve((size_t)B * sizeof(ffo::DevState));
   const size_t hCt_o = hcarve((size_t)B * sizeof(ffo::DevControl));
-  const size_t hteam_o = hcarve(nslot * 4 * tp.chunks.size()), hrank_o = hcarve(nslot * 4 * tp.chunks.size());
+  const size_t launches = reg ? 1 : tp.chunks.size();
+  const size_t hteam_o = hcarve(nslot * 4 * launches), hrank_o = hcarve(nslot * 4 * launches);
   const size_t host_bytes = hoff;
 
   Workspace* ws = nullptr;
@@ -2202,7 +2204,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
     std::fprintf(stderr,
                  "[ffo many] B %lld launches %zu resident %d (occupancy %d) | first launch: slice in LDS %d, state in "
                  "LDS %d (2: registers), %zu bytes | setup %.3f ms solve %.3f ms\n",
-                 (long long)B, reg ? 1 : tp.chunks.size(), reg ? rt.grid : W, occ, reg ? 2 : ckl[0], reg ? 2 : csl[0],
+                 (long long)B, launches, reg ? rt.grid : W, occ, reg ? 2 : ckl[0], reg ? 2 : csl[0],
                  reg ? 0 : clds[0], ms_setup, ms_iter);
   return collect_teams(B, n, hinfo, hstat, ms_setup, ms_iter, hCt, opt.verbose, infos);
 }

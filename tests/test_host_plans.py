@@ -31,6 +31,12 @@ def solve(n, m, T=0, **kw):
     return L.ffo_solve(n, 0, m, T, p, None, None, p, p, p, 1.5, p, p, p, p, 1e9, 1e-9, 1.0, 1.0, p if T else None,
                        options(verbose=1, **kw), None, p, None, ctypes.byref(ff._Info()))
 
+def many(sizes, m, **kw):
+    B, P = len(sizes), ctypes.c_void_p * len(sizes)
+    a = P(*[0x1000] * B)
+    return L.ffo_solve_many(B, (ctypes.c_int64 * B)(*sizes), 0, m, 0, a, None, None, a, a, a, a, a, a, a, None, 1.5, 1e9, 1e-9,
+                            1.0, 1.0, options(verbose=1, **kw), None, a, (ff._Info * B)())
+
 def batched(sizes, m, **kw):
     B = len(sizes)
     nb, offs = (ctypes.c_int64 * B)(*sizes), (ctypes.c_int64 * (B + 1))(0)
@@ -91,3 +97,11 @@ out.append(batched([7500] * 200, 10))
     assert out == [0, 0], err
     assert len(sizes) == 3 and sizes[0] == sizes[1] > 64 * 1_500_000 * 8
     assert sizes[2] < 13 * 1_500_000 * 8
+
+
+@pytest.mark.parametrize("call,B", [("batched", 65_536), ("batched", 131_072), ("many", 65_536)])
+def test_staging_grows_with_the_batch(fake, call, B):
+    """Pinned tables: a record of about 1 KB an instance, and two words for each of its workgroups."""
+    out, log, err = _run(fake, f"out = {call}([3] * {B}, 10)")
+    assert out == 0, err
+    assert sum(v for w, v in log if w == "host") < 1200 * B
