@@ -471,7 +471,7 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
     if (t.stream && need <= lds_cap && tile_bytes <= (size_t)8 << 30) { c = t; lds = need; }
     else tile_bytes = 0;
   }
-  if (reg) c.rc32 = c.prec == ffo::PREC_FP32 && c.lds_state;
+  if (reg) c.rc32 = c.prec == ffo::PREC_FP32;   // (the general kernel's state of so few assets is in LDS)
   // ---- workspace layout (one for both kernels) ----
   const size_t Pn = (size_t)P * n, Tpn = (size_t)Tp * n;
   size_t off = 0;
@@ -2156,7 +2156,11 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
     c.nwg = g[b];
     c.nw = (int)((n[b] + g[b] - 1) / g[b]);
     c.xmode = g[b] == 1 ? ffo::XM_LOCAL : ffo::XM_ATOMIC;
-    if (reg) { c.xgroups = reg_xgroups(g[b]); c.vmax = ffo::reg_vmax(rt.plan.ra); }
+    if (reg) {
+      c.xgroups = reg_xgroups(g[b]);
+      c.vmax = ffo::reg_vmax(rt.plan.ra);
+      c.rc32 = prec == ffo::PREC_FP32;   // as ffo_solve, whatever the other markets of the call
+    }
     hCt[b] = c;
   }
   HIPCHK(fill(Bd + oxb, xoff[B] * 8, 0u, hs));
@@ -2168,18 +2172,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
   // ---- LDS placement, records to the device, one cooperative launch per chunk ----
   std::vector<int> ckl, csl;
   std::vector<size_t> clds;
-  if (!reg) {
-    place_teams(tp, hP, hCt, prec, lds_lim, cus, ckl, csl, clds);
-  } else if (prec == ffo::PREC_FP32) {   // values rounded as where the general teams keep their state
-    std::vector<ffo::DevControl> t(B, c0);
-    for (int64_t b = 0; b < B; ++b) {
-      t[b].nwg = tp.g[b];
-      t[b].nw = (int)((n[b] + tp.g[b] - 1) / tp.g[b]);
-      t[b].xmode = tp.g[b] == 1 ? ffo::XM_LOCAL : ffo::XM_ATOMIC;
-    }
-    place_teams(tp, hP, t.data(), prec, lds_lim, cus, ckl, csl, clds);
-    for (int64_t b = 0; b < B; ++b) hCt[b].rc32 = t[b].lds_state;
-  }
+  if (!reg) place_teams(tp, hP, hCt, prec, lds_lim, cus, ckl, csl, clds);
   HIPCHK(hipMemcpyAsync(Bd + oP, hP, (size_t)B * sizeof(ffo::DevProblem), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oS, hS, (size_t)B * sizeof(ffo::DevState), hipMemcpyHostToDevice, hs));
   HIPCHK(hipMemcpyAsync(Bd + oCt, hCt, (size_t)B * sizeof(ffo::DevControl), hipMemcpyHostToDevice, hs));
