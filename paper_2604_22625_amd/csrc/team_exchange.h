@@ -164,13 +164,14 @@ __device__ __forceinline__ double conj15(double e, double a, double b, double d)
 }
 
 // prox of t'(a|x| + b|x|^d) at z (prox_cost of cost_math.h) for d = 3/2 and d = 2, with the step times a and b given.
+// (c is capped where its square would overflow, and the result is below 1e-300 r^2 anyway)
 __device__ __forceinline__ double prox15(double z, double ta, double tb, double d) {
   const double r = fmax(fabs(z) - ta, 0.0);
   double t;
   if (d == 2.0) {
     t = r / (1.0 + 2.0 * tb);
   } else {
-    const double c = 1.5 * tb, u = 2.0 * r * recip(c + root(fmax(fma(c, c, 4.0 * r), 1e-280)));
+    const double c = fmin(1.5 * tb, 1e150), u = 2.0 * r * recip(c + root(fmax(fma(c, c, 4.0 * r), 1e-280)));
     t = u * u;
   }
   return r <= 0.0 ? 0.0 : (z > 0.0 ? t : -t);
