@@ -67,7 +67,7 @@ struct DevState {
   double* y_out;                      // optional dual output
   double* snaps;                      // optional [ctl.snaps][2 n + nr + 2] iterates at checks (row-register kernel)
   const long long* clock0;            // optional device clock that ctl.time_limit_s counts from (row-register
-                                      // kernel); null: the team's own start
+                                      // kernel, many instances); null: the team's own start
   const double* w_init;               // optional [P][n] unscaled starting weights (else w0)
   const double* y_init;               // optional unscaled starting duals, y_out layout (else 0)
 };

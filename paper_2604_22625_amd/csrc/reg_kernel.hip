@@ -59,6 +59,7 @@ struct RegLds {
   double sc[NSC][NT];                    // a check's per-thread terms
   double c1[NSC], red[NWV][4];           // a check's sums
   int ok, restarts, checks, miss, miss_in, miss_out, rounds;
+  long long t_start;                     // thread 0's, many instances: the clock that the time limit counts from
 };
 
 // Sum over the waves of partial sum j (mx: the maximum for j = 1), in wave order.
@@ -321,7 +322,7 @@ __device__ __forceinline__ Place place(int tid0, int nwa, int nr) {
   return t;
 }
 
-template <int RA, int CA>
+template <int RA, int CA, bool QUEUE>
 __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* sp, const DevControl* cp, int wg,
                                          RegLds<RA, CA>& L, uint32_t first_spins) {
   const DevProblem& p = *pp;
@@ -338,6 +339,13 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
   const auto stored = [f32](double v, double z0) { return f32 ? z0 + (double)(float)(v - z0) : v; };   // an iterate
 
   RegX X = team_init(s, ctl, wg);
+  if constexpr (QUEUE) {
+    // (loaded per ticket these are vectors, and the first to be spilled: each reload is a trip to
+    // memory between an exchange's barrier and its totals.  2048 iterations of 64 instances with 140
+    // rows 52.7 and 46.2 ms; in a single solve, n = 5000, as scalars 29.3 ms against 28.7)
+    X.xbuf = glob(uni(s.xbuf));
+    X.bar = glob(uni(s.bar));
+  }
 
   double K[RA][CA];
   double x, yc, tx, ty, dc;   // the owned asset: iterates, their images, column scale
@@ -404,7 +412,11 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
       if (lane == 0) { L.part[wave][0] = a; L.part[wave][1] = b; }
       rows1(K, v, L.part[wave] + OR, tid);
       if (!exchange(X, L, tid, OS, false, pw == 0 ? first_spins : X.spin_limit)) goto fail;
-      if (pw == 0) t_start = wall_clock64();   // the team is complete
+      if constexpr (QUEUE) {
+        if (pw == 0 && tid == 0) L.t_start = s.clock0 ? *s.clock0 : wall_clock64();   // the call's start, or ...
+      } else {
+        if (pw == 0) t_start = wall_clock64();   // ... when the team is complete
+      }
       double kv = 0.0;
       for (int r = lane; r < NRP; r += 64) kv = fma(L.tot[OR + r], L.tot[OR + r], kv);
       kv = wave_sum(kv) + L.tot[1];
@@ -552,7 +564,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
             L.sc[6][tid] = mine ? ty * w0 : 0.0;
             L.sc[7][tid] = h;
             L.sc[8][tid] = wg == 0 && tid == 0 &&
-                           (double)(wall_clock64() - (s.clock0 ? *s.clock0 : t_start)) / ctl.wall_hz > ctl.time_limit_s;
+                           (double)(wall_clock64() - (QUEUE ? L.t_start : t_start)) / ctl.wall_hz > ctl.time_limit_s;
             L.sc[9][tid] = mine ? (isfinite(tx) ? 0.0 : 1.0) + (isfinite(ty) ? 0.0 : 1.0) : 0.0;
             L.sc[10][tid] = ex;
             L.sc[11][tid] = mine ? fabs(w) : 0.0;
@@ -692,7 +704,7 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
               s.info[IX_CHECKS] = (double)L.checks;
               s.info[IX_T_ITER] = (double)(t_end - t_loop) / ctl.wall_hz;
               s.info[IX_T_CHECK] = (double)t_check / ctl.wall_hz;
-              s.info[IX_T_POWER] = (double)(t_loop - t_start) / ctl.wall_hz;
+              s.info[IX_T_POWER] = (double)(t_loop - (QUEUE ? L.t_start : t_start)) / ctl.wall_hz;
               s.info[IX_MS_ROUNDS] = (double)L.rounds;
               s.info[IX_MISS_IN] = (double)L.miss_in;
               s.info[IX_MISS_OUT] = (double)L.miss_out;
@@ -755,7 +767,7 @@ template <int RA, int CA>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_reg(
     const DevProblem* __restrict__ dp, const DevState* __restrict__ ds, const DevControl* __restrict__ dc) {
   __shared__ RegLds<RA, CA> L;
-  reg_body<RA, CA>(dp, ds, dc, blockIdx.x, L, dc->spin_limit);
+  reg_body<RA, CA, false>(dp, ds, dc, blockIdx.x, L, dc->spin_limit);
 }
 
 // Many instances: resident workgroups take (instance, rank) tickets in order, an instance's
@@ -775,7 +787,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
     const int t = __builtin_amdgcn_readfirstlane(s_t);
     if (t >= tickets) return;
     const int b = inst[t];
-    reg_body<RA, CA>(dp + b, ds + b, dc + b, rank[t], L, 0xffffffffu);
+    reg_body<RA, CA, true>(dp + b, ds + b, dc + b, rank[t], L, 0xffffffffu);
   }
 }
 

@@ -26,6 +26,14 @@ __device__ __forceinline__ double uni(double x) {
              (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32)));
 }
 
+// A pointer likewise.
+template <class T>
+__device__ __forceinline__ T* uni(T* q) {
+  const unsigned long long u = (unsigned long long)q;
+  return (T*)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32)) << 32 |
+              (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u));
+}
+
 template <class T>
 using gptr = __attribute__((address_space(1))) T*;   // loads through it count against vmcnt only
 template <class T>
