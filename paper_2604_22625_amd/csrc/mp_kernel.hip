@@ -397,7 +397,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   long long t_check = 0;
   double omega = ctl.omega0 > 0.0 ? ctl.omega0 : 1.0, r0 = -1.0, rprev = INFINITY, lam = 0.0;
   long long it = 0;
-  int kk = 0, left = (int)min((long long)ctl.check_every, (long long)ctl.max_iter), status = DS_RUNNING;
+  uint32_t kk = 0;   // since the last restart (from 2^30 on the Halpern weights no longer matter)
+  int left = (int)min((long long)ctl.check_every, (long long)ctl.max_iter), status = DS_RUNNING;
 
   // ---- power iteration (see solve_kernel.hip)
   {
@@ -784,9 +785,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
           else {
             if (r0 < 0.0) r0 = uni(fpr);
             const bool rs = (fpr <= ctl.r_suff * r0) || (fpr <= ctl.r_nec * r0 && fpr > rprev) ||
-                            ((double)(kk + 1) >= ctl.r_art * (double)(it + 1));
+                            ((double)kk + 1.0 >= ctl.r_art * (double)(it + 1));
             restart = __builtin_amdgcn_readfirstlane(rs);
             rprev = uni(fpr);
+            kk = min(kk, 1u << 30);
             if (restart) {
               const double dxn = sqrt(c1[1]), dyn = sqrt(c1[2]);
               if (dxn > 1e-300 && dyn > 1e-300) omega = uni(sqrt(dyn / dxn) * sqrt(omega));   // half-way on a log scale

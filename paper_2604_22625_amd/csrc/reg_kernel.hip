@@ -395,7 +395,8 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
   long long t_check = 0;
   double omega = ctl.omega0 > 0.0 ? ctl.omega0 : 1.0, r0 = -1.0, rprev = INFINITY;
   long long it = 0;
-  int kk = 0, left = (int)min((long long)ctl.check_every, (long long)ctl.max_iter);   // iterations to the next check
+  uint32_t kk = 0;   // since the last restart (from 2^30 on the Halpern weights no longer matter)
+  int left = (int)min((long long)ctl.check_every, (long long)ctl.max_iter);   // iterations to the next check
   int status = DS_RUNNING;
 
   // ---- power iteration: lambda ~ ||K~ v||^2 / ||v||^2, v <- K~^T K~ v / (lambda ||v||)
@@ -668,9 +669,10 @@ __device__ __forceinline__ void reg_body(const DevProblem* pp, const DevState* s
           else {
             if (r0 < 0.0) r0 = uni(fpr);
             const bool rs = (fpr <= ctl.r_suff * r0) || (fpr <= ctl.r_nec * r0 && fpr > rprev) ||
-                            ((double)(kk + 1) >= ctl.r_art * (double)(it + 1));
+                            ((double)kk + 1.0 >= ctl.r_art * (double)(it + 1));
             restart = __builtin_amdgcn_readfirstlane(rs);
             rprev = uni(fpr);
+            kk = min(kk, 1u << 30);
             if (restart) {
               const double dxn = sqrt(L.c1[1]), dyn = sqrt(L.c1[2]);
               if (dxn > 1e-300 && dyn > 1e-300) omega = uni(sqrt(dyn / dxn) * sqrt(omega));   // half-way on a log scale

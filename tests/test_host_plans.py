@@ -105,3 +105,28 @@ def test_staging_grows_with_the_batch(fake, call, B):
     out, log, err = _run(fake, f"out = {call}([3] * {B}, 10)")
     assert out == 0, err
     assert sum(v for w, v in log if w == "host") < 1200 * B
+
+
+def test_barrier_counts_past_32_bits(tmp_path):
+    """The team barrier's comparisons about the wrap of its exchange counter (some hours into a
+    solve): a workgroup waits until the last of its team has arrived, and no longer."""
+    src = tmp_path / "wrap.hip"
+    src.write_text(r"""
+#include "team_exchange.h"
+#include <cstdio>
+int main() {
+  for (int members : {2, 3, 20, 256})
+    for (uint64_t e = (1ull << 32) / members - 3; e < (1ull << 32) + 3; e += e == (1ull << 32) / members + 3 ? (1ull << 32) - 6 - e : 1) {
+      const uint32_t want = ffo::arrivals((uint32_t)e, members);
+      for (int a = 0; a < 2 * members; ++a)
+        if (ffo::reached((uint32_t)(e * members + a), want) != (a >= members)) return printf("%d %llu %d\n", members, (unsigned long long)e, a), 1;
+      if (ffo::reached((uint32_t)e, (uint32_t)e + 1) || !ffo::reached((uint32_t)(e + 1), (uint32_t)e + 1)) return 2;
+    }
+  return 0;
+}
+""")
+    exe = str(tmp_path / "wrap")
+    r = subprocess.run([build.hipcc()] + build.flags() + ["-I", build.CSRC, "-o", exe, str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
