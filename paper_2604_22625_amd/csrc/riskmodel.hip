@@ -30,13 +30,14 @@
 namespace ffo {
 namespace {
 
-constexpr int RM_NT = 256, RM_W = RM_NT / 64;   // threads and waves of a workgroup
 constexpr int RM_TILE = 16;                     // assets of a workgroup
-constexpr int RM_GROUPS = RM_NT / RM_TILE;      // threads per asset
 constexpr int RM_CHUNK = 512;                   // days of factor returns in LDS at a time
 constexpr int RM_U = 4;                         // days of a thread per step, and in flight
 constexpr int RM_XCDS = 8;
-static_assert(RM_CHUNK % (RM_U * RM_GROUPS) == 0, "a step stays in its chunk");
+// 512 threads a workgroup for windows of at least so many days, where one workgroup per compute unit
+// holds the assets: the days in steps of 256 threads took 285 us against 206 at 32,000 days x 8 assets, p = 3,
+// and 85 against 70 at 4000 x 8, p = 6; at 4000 x 20,000, where the chip is full, 254 against 294.
+constexpr int RM_LONG = 2048, RM_FEW = 256;
 
 template <int P>
 struct RmDim {
@@ -44,10 +45,17 @@ struct RmDim {
   static constexpr int NV = G + P + 3 + P;     // + cross, sum r, sum r^2, count, factor sums
 };
 
-template <int P>
+// NT: threads of a workgroup.
+template <int NT>
+struct RmShape {
+  static constexpr int W = NT / 64, GROUPS = NT / RM_TILE;   // waves; threads per asset
+  static_assert(RM_CHUNK % (RM_U * GROUPS) == 0, "a step stays in its chunk");
+};
+
+template <int P, int NT>
 union RmLds {
-  double fs[RM_CHUNK * P];                          // factor returns of a chunk of days
-  double red[(RM_W + 1) * RmDim<P>::NV * RM_TILE];  // the waves' sums, then the totals
+  double fs[RM_CHUNK * P];                                       // factor returns of a chunk of days
+  double red[(RmShape<NT>::W + 1) * RmDim<P>::NV * RM_TILE];     // the waves' sums, then the totals
 };
 
 // The p x p system and the residual variance of asset i from its sums in LDS, value v at
@@ -124,17 +132,17 @@ __device__ __forceinline__ void solve_asset(const double* s, int min_obs, int i,
 }
 
 // Sigma_f = (Fr - mean)^T (Fr - mean) / (days - 1) by one workgroup, centred in a second pass
-// over the days: in each, wave w sums the entries w, w + RM_W, ... over the chunk in LDS.
-template <int P>
+// over the days: in each, wave w sums the entries w, w + W, ... over the chunk in LDS.
+template <int P, int NT>
 __device__ __forceinline__ void factor_cov(int days, const double* __restrict__ Fr, double* __restrict__ Sf, double* fs,
                                            double* mu) {
-  constexpr int G = RmDim<P>::G, NE = (G + RM_W - 1) / RM_W;
+  constexpr int W = RmShape<NT>::W, G = RmDim<P>::G, NE = ((G > P ? G : P) + W - 1) / W;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int ea[NE], eb[NE];
   double s[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) {   // entry (ea, eb) of the upper triangle, row-major
-    int a = 0, r = min(wave + e * RM_W, G - 1);
+    int a = 0, r = min(wave + e * W, G - 1);
     while (r >= P - a) { r -= P - a; ++a; }
     ea[e] = a;
     eb[e] = a + r;
@@ -145,12 +153,12 @@ __device__ __forceinline__ void factor_cov(int days, const double* __restrict__ 
     for (int k0 = 0; k0 < days; k0 += RM_CHUNK) {
       const int nk = min(RM_CHUNK, days - k0);
       __syncthreads();
-      for (int e = tid; e < nk * P; e += RM_NT) fs[e] = Fr[(size_t)k0 * P + e];
+      for (int e = tid; e < nk * P; e += NT) fs[e] = Fr[(size_t)k0 * P + e];
       __syncthreads();
       for (int k = lane; k < nk; k += 64) {
         if (pass == 0) {   // (at least as many entries as means)
 #pragma unroll
-          for (int e = 0; e < NE; ++e) s[e] += fs[k * P + min(wave + e * RM_W, P - 1)];
+          for (int e = 0; e < NE; ++e) s[e] += fs[k * P + min(wave + e * W, P - 1)];
         } else {
 #pragma unroll
           for (int e = 0; e < NE; ++e) s[e] = fma(fs[k * P + ea[e]] - mu[ea[e]], fs[k * P + eb[e]] - mu[eb[e]], s[e]);
@@ -161,7 +169,7 @@ __device__ __forceinline__ void factor_cov(int days, const double* __restrict__ 
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
         const double t = wave_sum(s[e]);
-        if (lane == 0 && wave + e * RM_W < P) mu[wave + e * RM_W] = t / (double)days;
+        if (lane == 0 && wave + e * W < P) mu[wave + e * W] = t / (double)days;
       }
       __syncthreads();
     }
@@ -169,24 +177,24 @@ __device__ __forceinline__ void factor_cov(int days, const double* __restrict__ 
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
     const double v = wave_sum(s[e]) / (double)(days - 1);
-    if (lane == 0 && wave + e * RM_W < G) {
+    if (lane == 0 && wave + e * W < G) {
       Sf[ea[e] * P + eb[e]] = v;
       Sf[eb[e] * P + ea[e]] = v;
     }
   }
 }
 
-template <int P, bool MASKED>
-__global__ __launch_bounds__(RM_NT) __attribute__((amdgpu_waves_per_eu(2))) void k_risk(
+template <int P, bool MASKED, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_risk(
     int days, int n, int tiles, const double* __restrict__ R, const double* __restrict__ Fr,
     const uint8_t* __restrict__ mask, int min_obs, double* __restrict__ beta, double* __restrict__ Sf,
     double* __restrict__ D, int32_t* __restrict__ valid) {
-  constexpr int NV = RmDim<P>::NV, G = RmDim<P>::G;
-  __shared__ RmLds<P> L;
+  constexpr int NV = RmDim<P>::NV, G = RmDim<P>::G, W = RmShape<NT>::W, GROUPS = RmShape<NT>::GROUPS;
+  __shared__ RmLds<P, NT> L;
   __shared__ double mu[P];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (blockIdx.x == 0) {   // (first, so that it is not the last one to start)
-    factor_cov<P>(days, Fr, Sf, L.fs, mu);
+    factor_cov<P, NT>(days, Fr, Sf, L.fs, mu);
     return;
   }
   // neighbouring tiles on one XCD: a line of the mask holds eight tiles' days
@@ -207,22 +215,22 @@ __global__ __launch_bounds__(RM_NT) __attribute__((amdgpu_waves_per_eu(2))) void
   const auto load = [&](double (&r)[RM_U], uint8_t (&m)[RM_U], int k) {
 #pragma unroll
     for (int u = 0; u < RM_U; ++u) {
-      const size_t at = (size_t)min(k + u * RM_GROUPS, days - 1) * n;
+      const size_t at = (size_t)min(k + u * GROUPS, days - 1) * n;
       r[u] = Rc[at];
       m[u] = MASKED ? Mc[at] : (uint8_t)1;
     }
   };
   load(rv, mv, grp);
-  for (int k0 = 0; k0 < days; k0 += RM_U * RM_GROUPS) {
+  for (int k0 = 0; k0 < days; k0 += RM_U * GROUPS) {
     if (k0 % RM_CHUNK == 0) {
       __syncthreads();
-      for (int e = tid; e < min(RM_CHUNK, days - k0) * P; e += RM_NT) L.fs[e] = Fr[(size_t)k0 * P + e];
+      for (int e = tid; e < min(RM_CHUNK, days - k0) * P; e += NT) L.fs[e] = Fr[(size_t)k0 * P + e];
       __syncthreads();
     }
-    load(rn, mn, k0 + RM_U * RM_GROUPS + grp);
+    load(rn, mn, k0 + RM_U * GROUPS + grp);
 #pragma unroll
     for (int u = 0; u < RM_U; ++u) {
-      const int k = k0 + u * RM_GROUPS + grp;
+      const int k = k0 + u * GROUPS + grp;
       const bool ob = col && k < days && mv[u] != 0;
       const double* fs = L.fs + min(k, days - 1) % RM_CHUNK * P;
       double f[P];   // zero on a day that does not count, so that its terms are zero
@@ -258,25 +266,33 @@ __global__ __launch_bounds__(RM_NT) __attribute__((amdgpu_waves_per_eu(2))) void
     if (vv < NV) L.red[(wave * NV + vv) * RM_TILE + a] = t;
   }
   __syncthreads();
-  for (int e = tid; e < NV * RM_TILE; e += RM_NT) {
+  for (int e = tid; e < NV * RM_TILE; e += NT) {
     double t = L.red[e];
 #pragma unroll
-    for (int w = 1; w < RM_W; ++w) t += L.red[w * NV * RM_TILE + e];
-    L.red[RM_W * NV * RM_TILE + e] = t;
+    for (int w = 1; w < W; ++w) t += L.red[w * NV * RM_TILE + e];
+    L.red[W * NV * RM_TILE + e] = t;
   }
   __syncthreads();
-  if (tid < RM_TILE && col) solve_asset<P>(L.red + RM_W * NV * RM_TILE + tid, min_obs, i, beta, D, valid);
+  if (tid < RM_TILE && col) solve_asset<P>(L.red + W * NV * RM_TILE + tid, min_obs, i, beta, D, valid);
+}
+
+template <int P, int NT>
+int launch_nt(int days, int n, const double* R, const double* Fr, const uint8_t* mask, int min_obs, double* beta,
+              double* Sf, double* D, int32_t* valid, hipStream_t st) {
+  const int tiles = (n + RM_TILE - 1) / RM_TILE, grid = 1 + (tiles + RM_XCDS - 1) / RM_XCDS * RM_XCDS;
+  if (mask)
+    hipLaunchKernelGGL((k_risk<P, true, NT>), dim3(grid), dim3(NT), 0, st, days, n, tiles, R, Fr, mask, min_obs, beta, Sf, D, valid);
+  else
+    hipLaunchKernelGGL((k_risk<P, false, NT>), dim3(grid), dim3(NT), 0, st, days, n, tiles, R, Fr, mask, min_obs, beta, Sf, D, valid);
+  return (int)hipGetLastError();
 }
 
 template <int P>
 int launch_rm(int days, int n, const double* R, const double* Fr, const uint8_t* mask, int min_obs, double* beta,
               double* Sf, double* D, int32_t* valid, hipStream_t st) {
-  const int tiles = (n + RM_TILE - 1) / RM_TILE, grid = 1 + (tiles + RM_XCDS - 1) / RM_XCDS * RM_XCDS;
-  if (mask)
-    hipLaunchKernelGGL((k_risk<P, true>), dim3(grid), dim3(RM_NT), 0, st, days, n, tiles, R, Fr, mask, min_obs, beta, Sf, D, valid);
-  else
-    hipLaunchKernelGGL((k_risk<P, false>), dim3(grid), dim3(RM_NT), 0, st, days, n, tiles, R, Fr, mask, min_obs, beta, Sf, D, valid);
-  return (int)hipGetLastError();
+  return days < RM_LONG || n > RM_FEW * RM_TILE
+             ? launch_nt<P, 256>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st)
+             : launch_nt<P, 512>(days, n, R, Fr, mask, min_obs, beta, Sf, D, valid, st);
 }
 
 }  // namespace
