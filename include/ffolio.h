@@ -60,7 +60,13 @@ typedef enum {
                               float64 restart anchors; the scaled constraint slice and
                               per-asset data copies in float32; every reduction, the
                               budget multipliers, checks, restarts and the KKT residual
-                              in float64 against the float64 inputs                  */
+                              in float64 against the float64 inputs.  Time per iteration against
+                              FFO_FP64: less where rows stream from device memory (n = 400,000,
+                              140 rows: 79 and 112 us); for one period otherwise the same to 10%
+                              more up to about 16,000 (140 rows) to 32,000 (32 rows) assets, and
+                              up to twice beyond (n = 60,000, 70 rows: 28 and 17 us); more for
+                              several periods (T = 20: 65 and 26 us) and in ffo_solve_batched
+                              (256 instances: 0.51 and 0.17 s)                         */
   FFO_FP32_BF16K = 2       /* batched solver only: as FP32, with the scaled constraint
                               rows rounded to bfloat16 (to nearest even, through float)
                               for the iteration and the checks alike, so the solve
@@ -73,7 +79,12 @@ typedef enum {
 typedef struct {
   double tol_rel_kkt;      /* stop when the relative KKT error <= tol (default 1e-6)  */
   int64_t max_iter;        /* iteration cap (default 1000000)                          */
-  double time_limit_s;     /* wall-clock cap per solve (default 360, paper Sec. 4.1)  */
+  double time_limit_s;     /* wall-clock cap per solve (default 360, paper Sec. 4.1).  The lockstep
+                              form of ffo_solve_batched, and the default form that gives its
+                              results, count it from the start of the call's iterations, for all
+                              instances together; the team form and ffo_solve_many for each
+                              instance from its own first iteration, so that a call whose
+                              instances wait for compute units may take longer               */
   int32_t check_every;     /* iterations between FP64 checks (default 64)             */
   int32_t precision;       /* ffo_precision (default FFO_FP64)                        */
   double restart_suff;     /* restart when residual <= suff * residual at restart (0.2) */
@@ -86,7 +97,9 @@ typedef struct {
   int32_t deterministic;   /* 1: partial sums exchanged through per-workgroup slots and
                               added in a fixed order, so repeated solves are bitwise
                               identical (slower); 0 (default): device-scope atomic adds,
-                              whose order varies from run to run                     */
+                              whose order varies from run to run.  ffo_solve_batched takes the
+                              lockstep form for it (fixed order); its team form and
+                              ffo_solve_many ignore it                               */
   int32_t speculative;     /* 1: one exchange per iteration (the multiplier's affine
                               correction); 0: separate statistics and row exchanges;
                               -1 (default): 1 for single-period, 0 for multi-period   */
@@ -102,7 +115,10 @@ typedef struct {
                               iteration per step, the products over the shared rows run as
                               float64 matrix-core GEMMs; FFO_FP64 only); 0 (default): where
                               the lockstep form applies (FFO_FP64, m + k <= 160) its results,
-                              from whichever form computes them faster, else the team form */
+                              from whichever form computes them faster, else the team form.
+                              (An instance that converged on its team within max_iter is
+                              FFO_OK, also where the lockstep form's hand-off of the last
+                              instances would have needed more iterations)             */
   int32_t autotune;        /* lockstep form's kernels only.  1 (default): on the first solve of a shape
                               the library times a few tile sizes and kernel arrangements and
                               keeps the fastest for later solves of that shape; -1: fixed
@@ -262,15 +278,17 @@ ffo_status ffo_adjoint(int64_t n, int64_t k, int64_t m, int64_t T,
  *     few kernels replayed from a captured graph: the products over the shared rows as
  *     float64 matrix-core GEMMs with ragged columns, then per-instance passes (budget
  *     multiplier, dual prox, Halpern step); converged instances are compacted out at
- *     every check; tile sizes come from the library's autotuner (opt->autotune).  The
- *     default for FFO_FP64 with m + k <= 160, B <= 65536, n_max <= 2^22.
+ *     every check; tile sizes come from the library's autotuner (opt->autotune).  For
+ *     FFO_FP64 with m + k <= 160, B <= 65536, n_max <= 2^22, where it is the default; the
+ *     default runs it on teams, with its results, where that is faster (d = 3/2 or 2, and
+ *     no more assets in all than keep the compute units busy for long).
  *   teams: each instance runs the solve kernel's loop on a team of workgroups sized to
- *     its asset count (spare resident workgroups go to the teams with the most assets per
- *     workgroup, down to 128 assets each; constraint slice and per-asset state in LDS when
- *     every team of the launch fits); all teams of a launch are resident at once and
- *     never wait for each
- *     other (batches larger than the resident grid run in several launches, largest
- *     instances first).  Every precision.
+ *     its asset count, in every precision.  FFO_FP64 with d = 3/2 or 2 and m + k <= 160: one
+ *     launch, whose resident workgroups take the instances in turn, largest first.  Otherwise
+ *     spare resident workgroups go to the teams with the most assets per workgroup, down to 128
+ *     assets each (constraint slice and per-asset state in LDS when every team of the launch
+ *     fits); all teams of a launch are resident at once and never wait for each other, and
+ *     batches larger than the resident grid run in several launches, largest instances first.
  * opt->precision: FFO_FP64, FFO_FP32 or FFO_FP32_BF16K (the last two: team form);
  * opt->workgroups is ignored; statuses as in ffo_solve.
  * Returns FFO_OK if every instance converged, else the most severe instance status
@@ -289,11 +307,13 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
  * specific vols, costs, exposure rows, bounds and (T > 0) terminal target, with k factors,
  * m exposure rows and T shared by all.  Each instance gets ffo_solve's setup (its own
  * scaled rows and scales), then one team of workgroups runs the solve kernel's loop for
- * it, as in ffo_solve_batched's team form: teams sized to n[b] (spare resident workgroups
- * go to the teams with the most assets per workgroup, down to 128 assets each; at most
- * 2048 assets per workgroup, fewer when T periods of staging would not fit in LDS),
- * constraint slice and state in LDS when every team of a launch fits, several launches
- * when the minimal teams exceed the resident grid.
+ * it, as in ffo_solve_batched's team form: for T = 0, in FFO_FP32 too, one launch that takes
+ * the markets in turn, and a market's result does not depend on the others; otherwise teams
+ * sized to n[b] (spare resident workgroups go to the teams with the most assets per workgroup,
+ * down to 128 assets each; at most 2048 assets per workgroup, fewer when T periods of staging
+ * would not fit in LDS), constraint slice and state in LDS when every team of a launch fits,
+ * several launches when the minimal teams exceed the resident grid.  (Ten markets of T = 10,
+ * n = 2000 in FFO_FP64 take 1.15 s in one call and 1.10 s in ten calls of ffo_solve.)
  * Host: n [B] (1 <= n[b] <= 2^24), infos [B], and the arrays of B device pointers, with
  * P = T - 1 decisions and T trades (P = T = 1 when T = 0):
  *   alpha: [P][n[b]];  s, q: [T][n[b]];  delta, w0: [n[b]];  F: [n[b]][k];  Omega: [k][k];
@@ -324,7 +344,7 @@ ffo_status ffo_solve_many(int64_t B, const int64_t* n, int64_t k, int64_t m, int
  *   R      [days][n]  asset returns (device)
  *   Fr     [days][p]  factor returns (device), 1 <= p <= 8 (the paper: p = 6)
  *   mask   [days][n]  optional (device, NULL = all observed): nonzero where R holds an
- *                     observation; unobserved entries are never read (they may be NaN)
+ *                     observation; what unobserved entries hold does not matter (NaN included)
  *   min_obs           assets with fewer observed days get no loadings (the paper: at
  *                     least two months of history)
  * Outputs (device, caller-allocated):

@@ -444,6 +444,7 @@ ffo_status solve_impl(int64_t n, int64_t k, int64_t m, int64_t T, const double* 
   // FP32 up to 64 workgroups (n = 4935, 70 rows 14.6 and 7.5): a solve that its budget of
   // iterations cuts off shows which way single float roundings fell, 2e-8 of the weights
   // between the two kernels at n = 59,140 and 512 iterations, 1e-8 between two runs of one.
+  // (What that leaves to the general kernel: n = 60,000, 70 rows 28 us, where FP64 takes 17 here.)
   ffo::RegPlan rp{};
   const bool reg = T == 0 && !opt.deterministic && opt.workgroups == 0 && c.spec &&
                    opt.verbose < 2 && (d == 1.5 || d == 2.0) && ffo::reg_plan(n, nr, cus, &rp) &&
@@ -741,7 +742,8 @@ hipError_t ls_start(const ffo::LsShared& S, const LsTune& tu, int gA, int gC, co
 constexpr int64_t kHandoff = 4;
 
 // Checks of which the row-register teams that stand in for the lockstep form keep the iterates
-// of every instance: the longest of 256 ran 17 checks past the hand-off.
+// of every instance: the longest of 256 ran 17 checks past the hand-off, at 64 iterations a check
+// (at a few iterations a check the second run up to the hand-off is the rule).
 constexpr int64_t kSnaps = 32;
 
 // Seconds of host time since `t`.
@@ -1171,7 +1173,8 @@ ffo_status launch_teams(const TeamPlan& tp, int W, const std::vector<int>& ckl, 
 
 // The teams of many single-period instances on the row-register kernel: one plan (rows
 // and assets per lane) for all, each instance's workgroups, and the ticket order (decreasing
-// size, so that the longest solves start first).
+// size, so that the longest solves start first).  `deterministic` asks nothing of teams, here or
+// on the general kernel.
 struct RegTeams {
   ffo::RegPlan plan{};
   std::vector<int> g;        // workgroups per instance

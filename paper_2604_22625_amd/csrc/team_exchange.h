@@ -142,7 +142,7 @@ __device__ __forceinline__ RegX team_init(const DevState& s, const DevControl& c
   return X;
 }
 
-// 1 / x and sqrt(x) by Newton steps on the hardware's estimates (x normal and positive;
+// 1 / x and sqrt(x) by Newton's and Goldschmidt's iterations on the hardware's estimates (x normal and positive;
 // within 1 ulp, without the scaling of subnormal and huge operands that the library's have).
 __device__ __forceinline__ double recip(double x) {
   double y = __builtin_amdgcn_rcp(x);
