@@ -10,7 +10,8 @@ Roofline: the dominant kernel is the persistent solve kernel (one launch per sol
 Algorithmic bytes per PDHG iteration follow the streaming model
     B_iter = 2 (m+k) n w + n (4P + 5T' + 3) w,   w = 8 bytes,
 i.e. the constraint rows read once for K^T y and once for K x, plus the per-asset
-vectors; achieved = iterations x B_iter / kernel time, measured per launch with HIP
+vectors (a model of the work: the kernel of this workload holds the rows in registers, so
+these bytes are not memory traffic); achieved = iterations x B_iter / kernel time, measured per launch with HIP
 events recorded by the library on the solve stream around the kernel launch.
 traffic = hardware bytes per launch (rocprofv3 FETCH_SIZE and WRITE_SIZE, scaled by a
 known-size copy; stored in profiles/) / the same kernel time, in GB/s; null when the
@@ -32,8 +33,8 @@ if ROOT not in sys.path:
 
 METRIC = "solves/s to 1e-6 rel KKT (n=5000; T=20); batched/FP32 vs plain; HBM % peak"
 HBM_PEAK_GBS = 8000.0
-COUNTERS = os.path.join(ROOT, "profiles", "k_solve_n5000_fp64.md")
-KERNEL_SOURCES = ["solve_kernel.hip", "setup_kernels.hip", "ffolio_host.hip", "internal.h", "cost_math.h"]
+COUNTERS = os.path.join(ROOT, "profiles", "k_reg_n5000_fp64.md")
+KERNEL_SOURCES = ["reg_kernel.hip", "team_exchange.h", "wave_ops.h", "setup_kernels.hip", "ffolio_host.hip", "internal.h"]
 
 
 def kernel_source_hash():
@@ -378,7 +379,7 @@ def comparisons(ff, torch, dev, dev_insts, tol, plain_value):
     out["risk_model_days504_n5000_p6"] = {"ms": ms, "algorithmic_bytes": rm_bytes,
                                           "achieved_gb_s": rm_bytes / (ms * 1e-3) / 1e9,
                                           "frac_of_hbm_peak": rm_bytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                                          "note": "ffo_risk_model call (partial sums, per-asset solves, factor "
+                                          "note": "ffo_risk_model call (one launch: sums, per-asset solves, factor "
                                                   "covariance) timed with events on the current stream"}
     out["adjoint_T10_n2000"] = {"forward_precision": "fp32", "forward_plus_backward_ms": dt * 1e3,
                                 "forward_kernel_ms": finfo.ms_iter, "forward_iters": finfo.iters,
@@ -390,9 +391,9 @@ def comparisons(ff, torch, dev, dev_insts, tol, plain_value):
 
 def stress_leg(ff, torch, n, steps=1, warmup=1, tol=1e-6, precision="fp64", ref=None):
     """Single-period solves at n assets (k=60, m=80, seed 5): the constraint rows (140 x n)
-    stay in device memory and are streamed twice per iteration, so this is the form whose
+    stay in device memory and are streamed once per iteration, so this is the form whose
     roofline is HBM bandwidth.  Algorithmic bytes per iteration as for the headline
-    workload, in the form's element size (the FP32 form reads float rows and float
+    workload but for that, in the form's element size (the FP32 form reads float rows and float
     iterate offsets).  Returns (record, W); with ``ref`` (an FP64 solution) the record
     states the largest weight difference against it."""
     from synth import make_single
@@ -415,7 +416,7 @@ def stress_leg(ff, torch, n, steps=1, warmup=1, tol=1e-6, precision="fp64", ref=
            "us_per_iter": kms * 1e3 / iters, "bytes_per_iter": bpi,
            "achieved_gb_s": bpi * iters / (kms * 1e-3) / 1e9,
            "frac_of_hbm_peak": bpi * iters / (kms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-           "rows_bytes": 140 * n * w, "status_all_ok": all(i.status == 0 for i in infos),
+           "rows_bytes": 140 * n * w, "note": "the rows counted as read once per iteration, as from tiles", "status_all_ok": all(i.status == 0 for i in infos),
            "rel_kkt_max": max(i.rel_kkt for i in infos)}
     if ref is not None:
         out["w_max_abs_diff_vs_fp64"] = float(torch.max(torch.abs(W - ref)))
