@@ -268,8 +268,9 @@ def solve_batched(batch: dict, *, tol: float = 1e-6, max_iter: int = 1_000_000, 
     ``synth.make_batch``: n_b, offs, n_max, F, Omega, delta, A shared; alpha, s, q, w0
     packed; L, U [B][m]).  ``form``: "lockstep" (every unconverged instance advances one
     iteration per step, the shared-row products on the matrix cores; FP64), "teams" (one
-    team of workgroups per instance) or "auto" (lockstep when it applies).  Returns
-    (w packed [N] float64 CUDA tensor, list of Info)."""
+    team of workgroups per instance) or "auto" (the lockstep form's results where it
+    applies, from whichever form is faster).  Returns (w packed [N] float64 CUDA tensor,
+    list of Info)."""
     torch = _torch()
     if not torch.cuda.is_available():
         raise FolioError(3, "no GPU visible to PyTorch: the solver has no CPU path")
