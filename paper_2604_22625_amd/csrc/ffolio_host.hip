@@ -1878,8 +1878,9 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
   // iteration count of the (kHandoff + 1)-th longest solve.  The longer ones go on from their
   // iterates there; those that ran more than kSnaps checks past it, or kept none, run again up
   // to it first (the same iterations, all of them side by side).  An instance keeps the result of
-  // its team where its continuation runs into the call's time limit, or converges no more within
-  // max_iter (a restart from the iterate alone takes up to half as many iterations again).
+  // its team where its continuation finds no memory, runs into the call's time limit, or converges
+  // no more within max_iter (a restart from the iterate alone takes up to half as many iterations
+  // again).
   std::vector<int64_t> its(B);
   for (int64_t b = 0; b < B; ++b) its[b] = infos[b].iters;
   std::nth_element(its.begin(), its.begin() + kHandoff, its.end(), std::greater<int64_t>());
@@ -1947,10 +1948,11 @@ ffo_status ffo_solve_batched(int64_t B, const int64_t* n_b, int64_t n_max, int64
     if (seconds <= 0.0) break;
     if (!l.w) continue;
     ffo_info ib{};
-    if (ffo_status st = finish_plain(l.b, n_b[l.b], offs[l.b], n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U, d,
-                                     GMV, lambda1, lambda2, lambda3, opt, l.w, l.y, l.omega, at, l.restarts, seconds,
-                                     D(ohA), hs, D(ohx), &ib))
-      return st;
+    const ffo_status st = finish_plain(l.b, n_b[l.b], offs[l.b], n_max, k, m, F, Omega, delta, A, alpha, s, q, w0, L, U,
+                                       d, GMV, lambda1, lambda2, lambda3, opt, l.w, l.y, l.omega, at, l.restarts,
+                                       seconds, D(ohA), hs, D(ohx), &ib);
+    if (st == FFO_ENOMEM) continue;
+    if (st) return st;
     if (ib.status == FFO_TIMEOUT || (ib.status != FFO_OK && infos[l.b].status == FFO_OK)) continue;
     infos[l.b] = ib;
     HIPCHK(hipMemcpyAsync(w_out + offs[l.b], D(ohx), (size_t)n_b[l.b] * 8, hipMemcpyDeviceToDevice, hs));

@@ -1,7 +1,8 @@
 // A stand-in for the HIP calls that the library's host code makes, for tests of that code without
 // a GPU: "device" memory is zeroed host memory, copies are immediate and kernels do nothing.
-// fake_limit sets the size from which hipMalloc fails; fake_log returns the calls so far, one
-// "name value" a line.
+// fake_limit sets the size from which hipMalloc fails, fake_allow how many of its calls succeed;
+// fake_on_read a function called after each copy to the host, which may change what it reads;
+// fake_log returns the calls so far, one "name value" a line.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdlib>
@@ -9,7 +10,8 @@
 #include <string>
 
 namespace {
-size_t limit = ~(size_t)0;
+size_t limit = ~(size_t)0, allow = ~(size_t)0;
+void (*on_read)(void*, size_t) = nullptr;
 std::string calls;
 hipError_t last = hipSuccess;
 
@@ -19,6 +21,8 @@ void note(const char* what, size_t v) { calls += std::string(what) + " " + std::
 extern "C" {
 
 void fake_limit(size_t bytes) { limit = bytes; }
+void fake_allow(size_t count) { allow = count; }
+void fake_on_read(void (*f)(void*, size_t)) { on_read = f; }
 const char* fake_log() { return calls.c_str(); }
 
 void** __hipRegisterFatBinary(const void*) { static void* h; return &h; }
@@ -44,7 +48,8 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 10000
 
 hipError_t hipMalloc(void** p, size_t n) {
   note("malloc", n);
-  if (n >= limit) return last = hipErrorOutOfMemory;
+  if (n >= limit || allow == 0) return last = hipErrorOutOfMemory;
+  --allow;
   *p = std::calloc(1, n);
   return hipSuccess;
 }
@@ -56,7 +61,11 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
 }
 hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
 
-hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t) {
+  std::memcpy(d, s, n);
+  if (k == hipMemcpyDeviceToHost && on_read) on_read(d, n);
+  return hipSuccess;
+}
 hipError_t hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
 hipError_t hipMemsetAsync(void*, int, size_t, hipStream_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }

@@ -3,7 +3,7 @@ lockstep form it stands in for, whatever the number of instances that wait for a
 and an instance that converged within max_iter stays converged."""
 import pytest
 
-from synth import make_batch
+from synth import make_batch, make_single
 
 pytestmark = pytest.mark.gpu
 
@@ -34,6 +34,23 @@ def test_time_limit_covers_the_call(form, check_every):
     assert infos[0].ms_iter <= 1.5e3 * limit, infos[0].ms_iter
     assert {i.status for i in infos} in ({TIMEOUT}, {0, TIMEOUT})
     assert bool(torch.isfinite(W).all())
+
+
+def test_every_market_of_a_call_has_the_limit():
+    """ffo_solve_many and the team form count the limit for each instance: those that wait for a
+    compute unit get it too (5 us an iteration and one workgroup here, at most three of them waiting
+    in turn)."""
+    ff = _ff()
+    limit = 0.05
+    print("[case] time limit many", flush=True)
+    _, a = ff.solve_many([make_single(40 + j % 60, 4, 6, seed=j) for j in range(300)], tol=1e-30, max_iter=10**9,
+                         time_limit_s=limit, raise_on_failure=False)
+    _, b = ff.solve_batched(make_batch(600, 4, 6, seed=41, n_lo=40, n_hi=400), form="teams", tol=1e-30, max_iter=10**9,
+                            time_limit_s=limit, raise_on_failure=False)
+    for infos, waves in ((a, 2), (b, 3)):
+        late = [i.iters for i in infos if i.status == TIMEOUT]
+        assert late and min(late) * 10e-6 >= 0.5 * limit
+        assert infos[0].ms_iter <= 1.5e3 * limit * waves
 
 
 def test_instances_that_converged_in_time_keep_their_results():

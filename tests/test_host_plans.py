@@ -3,6 +3,7 @@ calls (fake_hip.cpp), in a process of its own, in which kernels do nothing and e
 once.  Checked is what the library allocates and what it does when that fails."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -17,9 +18,10 @@ import ctypes, json, os, sys
 sys.path.insert(0, {root!r})
 fake = ctypes.CDLL({fake!r}, mode=ctypes.RTLD_GLOBAL)
 fake.fake_log.restype = ctypes.c_char_p
-fake.fake_limit.argtypes = [ctypes.c_size_t]
+fake.fake_limit.argtypes = fake.fake_allow.argtypes = [ctypes.c_size_t]
+READ = ctypes.CFUNCTYPE(None, ctypes.c_void_p, ctypes.c_size_t)
 import paper_2604_22625_amd as ff
-L, p = ff.lib(), ctypes.c_void_p(0x1000)      # device arrays: never read
+L, p, INFOS = ff.lib(), ctypes.c_void_p(0x1000), [None]      # p: device arrays, never read
 
 def options(**kw):
     o = ff.default_options()
@@ -39,11 +41,12 @@ def many(sizes, m, **kw):
 
 def batched(sizes, m, **kw):
     B = len(sizes)
+    INFOS[0], W = (ff._Info * B)(), ctypes.create_string_buffer(8 * sum(sizes))
     nb, offs = (ctypes.c_int64 * B)(*sizes), (ctypes.c_int64 * (B + 1))(0)
     for b in range(B):
         offs[b + 1] = offs[b] + nb[b]
     return L.ffo_solve_batched(B, nb, max(sizes), 0, m, None, None, p, p, offs, p, p, p, p, p, p, 1.5, 1e9, 1e-9, 1.0, 1.0,
-                               options(verbose=1, **kw), None, p, (ff._Info * B)())
+                               options(verbose=1, **kw), None, W, INFOS[0]), [(i.status, i.iters) for i in INFOS[0]]
 
 """
 
@@ -88,10 +91,10 @@ def test_batch_without_room_for_iterates(fake):
     """200 instances of 7500 assets: a dozen vectors of 1.5 million entries, and 32 copies of two
     vectors for the hand-off."""
     out, log, err = _run(fake, """
-out = [batched([7500] * 200, 10)]
+out = [batched([7500] * 200, 10)[0]]
 L.ffo_release()
 fake.fake_limit(600_000_000)
-out.append(batched([7500] * 200, 10))
+out.append(batched([7500] * 200, 10)[0])
 """)
     sizes = [v for w, v in log if w == "malloc"]
     assert out == [0, 0], err
@@ -99,11 +102,43 @@ out.append(batched([7500] * 200, 10))
     assert sizes[2] < 13 * 1_500_000 * 8
 
 
+def test_iterates_beyond_a_gibibyte_are_not_kept(fake):
+    out, log, err = _run(fake, "out = [batched([7500] * 270, 10)[0], batched([7500] * 300, 10)[0]]")
+    assert out == [0, 0], err
+    assert [v for w, v in log if w == "malloc"][0] > 64 * 270 * 7500 * 8
+    out, log, err = _run(fake, "out = batched([7500] * 300, 10)[0]")
+    assert [v for w, v in log if w == "malloc"][0] < 13 * 300 * 7500 * 8
+
+
+HAND_OFF = """
+import struct
+B, LEN = 8, {len}
+def read(dst, n):       # the teams' records: instance b ended after 64 (b + 1) iterations, converged
+    if n == B * LEN * 8:
+        for b in range(B):
+            ctypes.memmove(dst + b * LEN * 8, struct.pack("d", 64.0 * (b + 1)), 8)
+cb = READ(read)
+fake.fake_on_read(cb)
+"""
+
+
+@pytest.mark.parametrize("mallocs", [2, 1])
+def test_hand_off_without_room_for_a_solve(fake, mallocs):
+    """The four longest of eight converged instances go on from their iterates at 256 iterations, in
+    a workspace of their own; where there is none left, they keep what their teams found."""
+    info_len = int(re.search(r"INFO_LEN = (\d+)", open(os.path.join(build.CSRC, "internal.h")).read())[1])
+    out, log, err = _run(fake, HAND_OFF.format(len=info_len) + f"fake.fake_allow({mallocs})\nout = batched([50] * 8, 10)")
+    assert out[0] == 0, (out, err)
+    assert sum(w == "malloc" for w, v in log) == (2 if mallocs == 2 else 5)     # (each instance tries)
+    ended = [64 * (b + 1) for b in range(8)] if mallocs == 1 else [64, 128, 192, 256, 256, 256, 256, 256]
+    assert out[1] == [[0, i] for i in ended]
+
+
 @pytest.mark.parametrize("call,B", [("batched", 65_536), ("batched", 131_072), ("many", 65_536)])
 def test_staging_grows_with_the_batch(fake, call, B):
     """Pinned tables: a record of about 1 KB an instance, and two words for each of its workgroups."""
     out, log, err = _run(fake, f"out = {call}([3] * {B}, 10)")
-    assert out == 0, err
+    assert (out[0] if call == "batched" else out) == 0, err
     assert sum(v for w, v in log if w == "host") < 1200 * B
 
 
