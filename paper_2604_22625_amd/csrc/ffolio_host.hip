@@ -1188,7 +1188,7 @@ struct RegTeams {
 // 8000), 491 and 567 at 1,024,000 and 577 and 714 at 1,280,000 (n = 8000); 70 rows 668 and 617 at
 // 2,000,000, 871 and 945 at 2,880,000, 1169 and 1278 at 4,000,000 (n = 8000); 40 rows 1004 and 909
 // at 3,200,000, 1770 and 1753 at 6,400,000; 10 rows 1278 and 1053 at 4,000,000, 3003 and 3244 at
-// 8,000,000 (n = 16,000).  (256 instances, n 500 to 8000, 70 rows, 720,000: 375 and 184.)
+// 8,000,000 (n = 16,000).  (256 instances, n 500 to 8000, 70 rows, 720,000: 375 and 173.)
 bool lockstep_faster(int64_t N, int nr, int cus) {
   return N > (int64_t)cus * (nr > 80 ? 4000 : nr > 48 ? 11000 : 25000);
 }
